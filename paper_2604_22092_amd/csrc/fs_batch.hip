@@ -97,7 +97,12 @@ struct fs_batch {
     fsi::HeavyArgs* d_htable = nullptr;
     uint32_t* d_hfirst = nullptr;
     fsi::RedArgs* d_red = nullptr;
-    uint32_t blocks = 0, hblocks = 0, hmembers = 0;
+    // the table's members by the kernel that runs them: kind 0 the streaming
+    // step, kind 1 + w the replica step with groups of 2^(2 + w) chunks;
+    // members of one kind are adjacent, with block ranges of their own
+    // (d_first + kfirst[kind])
+    uint32_t kat[4] = {}, kmembers[4] = {}, kblocks[4] = {}, kfirst[4] = {};
+    uint32_t hblocks = 0, hmembers = 0;
     uint32_t chunk = 0; // longest launch sequence (partial slots of the members)
     Staging staging;
 };
@@ -122,13 +127,24 @@ fs_status rebuild_tables(fs_batch* b)
 {
     const size_t M = b->members.size();
     std::vector<StepArgs> table;
-    std::vector<uint32_t> first(1, 0u), hfirst(1, 0u);
+    std::vector<uint32_t> first, hfirst(1, 0u);
     std::vector<fsi::HeavyArgs> htable;
     std::vector<fsi::RedArgs> red;
     b->chunk = 1u << 30;
+    for (uint32_t kind = 0; kind < 4; ++kind) {
+        b->kat[kind] = (uint32_t)table.size();
+        b->kfirst[kind] = (uint32_t)first.size();
+        uint32_t at = 0;
+        first.push_back(0u);
+        for (fs_sim* s : b->members) {
+            if ((s->lgW < 0 ? 0u : (uint32_t)s->lgW - 1u) != kind) continue;
+            table.push_back(s->args);
+            first.push_back(at += s->G);
+        }
+        b->kmembers[kind] = (uint32_t)table.size() - b->kat[kind];
+        b->kblocks[kind] = at;
+    }
     for (fs_sim* s : b->members) {
-        table.push_back(s->args);
-        first.push_back(first.back() + s->G);
         if (s->nseg && !s->hub_push) {
             htable.push_back(heavy_args(s));
             hfirst.push_back(hfirst.back() + heavy_grid(s));
@@ -140,17 +156,17 @@ fs_status rebuild_tables(fs_batch* b)
         r.G = s->G;
         r.C = 4u * (uint32_t)s->R;
         r.H = (uint32_t)s->H;
+        r.base = s->lgW >= 0 ? s->d_base : nullptr;
         red.push_back(r);
         b->chunk = std::min(b->chunk, s->chunk);
     }
-    b->blocks = first.back();
     b->hblocks = hfirst.back();
     b->hmembers = (uint32_t)htable.size();
     b->dirty = false;
     if (M == 0) return FS_OK;
     const size_t o_table = 0;
     const size_t o_first = align_up(o_table + M * sizeof(StepArgs));
-    const size_t o_htable = align_up(o_first + (M + 1) * sizeof(uint32_t));
+    const size_t o_htable = align_up(o_first + first.size() * sizeof(uint32_t));
     const size_t o_hfirst = align_up(o_htable + std::max<size_t>(htable.size(), 1) * sizeof(fsi::HeavyArgs));
     const size_t o_red = align_up(o_hfirst + hfirst.size() * sizeof(uint32_t));
     const size_t bytes = align_up(o_red + M * sizeof(fsi::RedArgs));
@@ -237,19 +253,28 @@ fs_status batch_sequence(fs_batch* b, uint32_t r)
     const uint32_t M = (uint32_t)b->members.size();
     // the instantiation with rate recording only when a member records them
     bool rates = false;
-    for (const fs_sim* s : b->members) rates = rates || s->d_rates != nullptr;
-    const void* kfn = fsk::step_batch_kernel_fn(b->storage, b->weighted == 1, rates);
+    for (fs_sim* s : b->members) {
+        rates = rates || s->d_rates != nullptr;
+        FS_HIP(refresh_base(s));
+    }
+    const void* kfn[4] = {fsk::step_batch_kernel_fn(b->storage, b->weighted == 1, rates),
+                          fsk::reps_kernel_fn(b->storage, 2, true), fsk::reps_kernel_fn(b->storage, 3, true),
+                          fsk::reps_kernel_fn(b->storage, 4, true)};
     const void* hfn = fsk::heavy_batch_kernel_fn(b->weighted == 1);
-    if (!kfn || !hfn) return fail(FS_ERR_DEVICE, "no batch kernel for this configuration");
+    if (!kfn[0] || !kfn[1] || !kfn[2] || !kfn[3] || !hfn) return fail(FS_ERR_DEVICE, "no batch kernel for this configuration");
     for (uint32_t j = 0; j < r; ++j) {
         uint32_t off = j;
         if (b->hmembers) {
             void* hargv[] = {&b->d_htable, &b->d_hfirst, &b->hmembers, &off};
             FS_HIP(hipLaunchKernel(hfn, dim3(b->hblocks), dim3(WG), hargv, 0, b->stream));
         }
-        uint32_t members = M;
-        void* argv[] = {&b->d_table, &b->d_first, &members, &off};
-        FS_HIP(hipLaunchKernel(kfn, dim3(b->blocks), dim3(fsi::STREAM_TPB), argv, 0, b->stream));
+        for (uint32_t kind = 0; kind < 4; ++kind) {
+            if (b->kmembers[kind] == 0) continue;
+            const StepArgs* table = b->d_table + b->kat[kind];
+            const uint32_t* first = b->d_first + b->kfirst[kind];
+            void* argv[] = {&table, &first, &b->kmembers[kind], &off};
+            FS_HIP(hipLaunchKernel(kfn[kind], dim3(b->kblocks[kind]), dim3(fsi::STREAM_TPB), argv, 0, b->stream));
+        }
     }
     void* rargv[] = {&b->d_red};
     FS_HIP(hipLaunchKernel(fsk::reduce_batch_kernel_fn(), dim3(r, M), dim3(fsi::RED_TPB), rargv, 0, b->stream));

@@ -35,6 +35,12 @@ constexpr uint32_t SUMMARY_BITS = 1u << 20;
 constexpr int UNIFORM_MAX_DEG = FS_UMAX;
 // Entries of the hazard table of a fixed-step sim (StepArgs::htab).
 constexpr uint32_t HTAB_LEN = 8192;
+// Replica step (fs_reps.hpp): the most light edges a row may have (counted in
+// bytes), the 64-unit chunks a sim needs to take it, and the groups (2^lgW
+// chunks, one wavefront each) it needs to take a larger lgW.
+constexpr int32_t REPS_MAX_DEG = 127;
+constexpr size_t REPS_CHUNKS = 8192;
+constexpr size_t REPS_GROUPS = 3072;
 // Bitmaps are allocated in whole 512-unit tiles (8 words of 64 bits).
 constexpr uint32_t BITMAP_TILE = 512;
 // Active-chunk compaction: the refresh runs one workgroup of WG_REFRESH
@@ -257,9 +263,10 @@ struct HeavyArgs {
 // workgroups, C = 4R counters each, summed into the H-slot history ring.
 struct RedArgs {
     Ctl* ctl;
-    const uint32_t* part;
+    uint32_t* part;
     uint32_t* hist;
     uint32_t G, C, H, pad;
+    uint32_t* base; // replica step: the counts before the sequence (see reduce_body), else nullptr
 };
 
 // Upper bound on step workgroups (they loop over tiles beyond it), chosen so

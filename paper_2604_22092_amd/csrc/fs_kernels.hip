@@ -32,14 +32,20 @@ namespace fsk {
 // a ticket in ctl->done once its reads of ctl->step are done, and the last
 // one adds r to ctl->step and clears the count (so the sequence needs no
 // launch of its own for the advance).
-__device__ __forceinline__ void reduce_body(Ctl* ctl, const uint32_t* part, uint32_t G, uint32_t C,
-                                            uint32_t* out, uint32_t H, uint32_t j, uint32_t r)
+// With a base, the partials are the replica step's transitions, [replica][S ->
+// E, E -> I, I -> R, unused]: block j leaves its totals in the first row of
+// slot j, and the last block walks the slots, turning base, the counts before
+// the sequence, into the counts after each step (r additions per counter:
+// 0.1 us per step, against a scan of every unit's state in the step).
+__device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G, uint32_t C, uint32_t* out,
+                                            uint32_t H, uint32_t j, uint32_t r, uint32_t* base)
 {
     __shared__ uint32_t s[RED_TPB];
+    __shared__ uint32_t s_last;
     const uint32_t t = threadIdx.x;
     // of a sequence longer than the ring only the last H steps are kept, so
     // no two blocks write one slot
-    if ((size_t)j + H >= (size_t)r) {
+    if (base || (size_t)j + H >= (size_t)r) {
         const uint32_t groups = RED_TPB / C;
         const uint32_t c = t % C;
         const uint32_t* p = part + (size_t)j * G * C + c;
@@ -58,33 +64,63 @@ __device__ __forceinline__ void reduce_body(Ctl* ctl, const uint32_t* part, uint
             __syncthreads();
         }
         if (t < C) {
-            const unsigned long long base = ctl ? ctl->step : 0ull;
-            out[(size_t)((base + j) % H) * C + t] = s[t];
+            const unsigned long long first = ctl ? ctl->step : 0ull;
+            if (base)
+                __hip_atomic_store(&part[(size_t)j * G * C + t], s[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+                out[(size_t)((first + j) % H) * C + t] = s[t];
         }
     }
     if (ctl) {
         __syncthreads();
         if (t == 0) {
             const uint32_t prior = __hip_atomic_fetch_add(&ctl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-            if (prior + 1u == r) {
-                __hip_atomic_store(&ctl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&ctl->step, ctl->step + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_last = prior + 1u == r;
+        }
+        __syncthreads();
+        if (!s_last) return;
+        if (base && t < C) {
+            // thread t carries counter t = (replica, compartment): it loses
+            // the transitions out of its compartment and gains those into it
+            const unsigned long long first = ctl->step;
+            const bool gain = (t & 3u) != 0u;
+            uint32_t n = base[t];
+            for (uint32_t i = 0; i < r; i += 8) {
+                uint32_t lost[8], got[8];
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u) {
+                    const uint32_t* p = part + (size_t)min(i + u, r - 1u) * G * C;
+                    lost[u] = __hip_atomic_load(&p[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    got[u] = gain ? __hip_atomic_load(&p[t - 1u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u) {
+                    if (i + u >= r) break;
+                    n += got[u] - lost[u];
+                    if ((size_t)(i + u) + H >= (size_t)r) out[(size_t)((first + i + u) % H) * C + t] = n;
+                }
             }
+            base[t] = n;
+        }
+        __syncthreads();
+        if (t == 0) {
+            __hip_atomic_store(&ctl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&ctl->step, ctl->step + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
 
-__global__ __launch_bounds__(RED_TPB) void reduce_kernel(Ctl* ctl, const uint32_t* part, uint32_t G,
-                                                     uint32_t C, uint32_t* out, uint32_t H)
+__global__ __launch_bounds__(RED_TPB) void reduce_kernel(Ctl* ctl, uint32_t* part, uint32_t G, uint32_t C,
+                                                         uint32_t* out, uint32_t H, uint32_t* base)
 {
-    reduce_body(ctl, part, G, C, out, H, blockIdx.x, gridDim.x);
+    reduce_body(ctl, part, G, C, out, H, blockIdx.x, gridDim.x, base);
 }
 
 // Batched reduce: block (j, m) sums slot j of member m (grid r x members).
 __global__ __launch_bounds__(RED_TPB) void reduce_batch_kernel(const RedArgs* __restrict__ table)
 {
     const RedArgs q = table[blockIdx.y];
-    reduce_body(q.ctl, q.part, q.G, q.C, q.hist, q.H, blockIdx.x, gridDim.x);
+    reduce_body(q.ctl, q.part, q.G, q.C, q.hist, q.H, blockIdx.x, gridDim.x, q.base);
 }
 
 // Summary of an infectivity bitmap: bit s is set when any of the 32 w units
@@ -403,8 +439,8 @@ hipError_t launch_recount(int storage, const void* state, int32_t n, int32_t lgR
         hipLaunchKernelGGL(recount_kernel<0>, dim3(g), dim3(WG), 0, s, state, n, lgR, replica, part);
     else
         hipLaunchKernelGGL(recount_kernel<1>, dim3(g), dim3(WG), 0, s, state, n, lgR, replica, part);
-    hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(RED_TPB), 0, s, (Ctl*)nullptr, (const uint32_t*)part,
-                       (uint32_t)g, 4u, out4, 1u);
+    hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(RED_TPB), 0, s, (Ctl*)nullptr, part, (uint32_t)g, 4u,
+                       out4, 1u, (uint32_t*)nullptr);
     return hipGetLastError();
 }
 

@@ -50,9 +50,10 @@ hipError_t launch_recount(int storage, const void* state, int32_t n, int32_t lgR
 // the row in replica r (StepArgs::hub_T).
 hipError_t launch_hub_recount(const int32_t* row_ptr, const int32_t* col_ind, int32_t hub_base, uint32_t hubs,
                               int32_t lgR, const uint32_t* bits, uint32_t* out, hipStream_t s);
-// reduce_kernel(Ctl*, const uint32_t* part, uint32_t G, uint32_t C, uint32_t* out, uint32_t H):
+// reduce_kernel(Ctl*, uint32_t* part, uint32_t G, uint32_t C, uint32_t* out, uint32_t H, uint32_t* base):
 // one block per slot, RED_TPB threads; with a ctl it also adds the slot count (its
-// grid) to the step index, which ends a launch sequence.
+// grid) to the step index, which ends a launch sequence.  base (only with a
+// ctl): the partials are the replica step's transitions, added to base.
 const void* reduce_kernel_fn();
 // Segment partials of degree-binned rows (HeavyArgs): heavy_pressure_kernel
 // (WG threads, bits from global memory), or with resident set
@@ -84,6 +85,14 @@ hipError_t launch_get_rates(const float* rates, float* dst, int32_t n, int32_t l
 hipError_t launch_seed(int storage, void* state, void* age, const int64_t* nodes, int64_t count, int32_t lgR,
                        int32_t replica, int32_t comp, hipStream_t s);
 hipError_t launch_clear_u32(uint32_t* p, size_t n, hipStream_t s);
+// The replica step (reps_kernel(StepArgs), REPS_TPB = STREAM_TPB threads) with
+// groups of 2^lgW chunks, lgW in {2, 3, 4}, or its batched form
+// reps_batch_kernel(const StepArgs*, const uint32_t* first, uint32_t members,
+// uint32_t step_off); nullptr for another lgW.
+const void* reps_kernel_fn(int storage, int lgW, bool batch);
+// Counts of every replica of `total` units into base[R][4].
+hipError_t launch_count_all(int storage, const void* state, uint32_t total, int32_t lgR, uint32_t* base,
+                            hipStream_t s);
 hipError_t launch_set_ctl(fsi::Ctl* ctl, unsigned long long step, hipStream_t s);
 hipError_t launch_eval_hazard(const fsi::HazardDev& h, int32_t storage, const void* ages, float* out, int64_t n,
                               hipStream_t s);

@@ -474,7 +474,8 @@ fs_status build_exec(fs_markov* m, uint32_t b)
         if ((st = add((const void*)&fsm::mk_push_kernel, dim3(push_grid(m)), dim3(fsm::PTPB), argv)) != FS_OK) return st;
         if ((st = add((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(fsm::MTPB), argv)) != FS_OK) return st;
     }
-    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H};
+    uint32_t* no_base = nullptr;
+    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H, &no_base};
     if ((st = add(fsk::reduce_kernel_fn(), dim3(q.r), dim3(fsi::RED_TPB), rargv)) != FS_OK) return st;
     FS_HIP(hipGraphInstantiate(&m->exec, m->graph, nullptr, nullptr, 0));
     return FS_OK;
@@ -491,7 +492,8 @@ fs_status launch_seq(fs_markov* m, uint32_t r)
                                m->stream));
         FS_HIP(hipLaunchKernel((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(fsm::MTPB), argv, 0, m->stream));
     }
-    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H};
+    uint32_t* no_base = nullptr;
+    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H, &no_base};
     FS_HIP(hipLaunchKernel(fsk::reduce_kernel_fn(), dim3(r), dim3(fsi::RED_TPB), rargv, 0, m->stream));
     return FS_OK;
 }

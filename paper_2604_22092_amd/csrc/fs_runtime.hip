@@ -256,7 +256,7 @@ void release_sim(fs_sim* s)
                         (void*)s->d_hist, (void*)s->d_part, (void*)s->d_rc_part, (void*)s->d_cnt4,
                         (void*)s->d_summary, s->d_seg_part, (void*)s->d_lam_part, (void*)s->d_dt_hist,
                         (void*)s->d_shed[0], (void*)s->d_shed[1], (void*)s->d_live, (void*)s->d_act,
-                        (void*)s->d_htab, (void*)s->d_laws, (void*)s->d_hub})
+                        (void*)s->d_htab, (void*)s->d_laws, (void*)s->d_hub, (void*)s->d_base})
             sim_free(s, p);
     }
     s->layout.reset();
@@ -282,9 +282,10 @@ struct SeqArgs {
     std::vector<fsi::HeavyArgs> heavy;
     std::vector<fsi::SumArgs> sum;
     fsi::Ctl* ctl;
-    const uint32_t* part;
+    uint32_t* part;
     uint32_t G, C, H, r;
     uint32_t* hist;
+    uint32_t* base;
     // compaction refresh
     const uint8_t* live;
     uint32_t nchunks, rows, n;
@@ -517,6 +518,77 @@ bool layout_cached(fs_graph* g, int32_t R, int32_t heavy_deg, int32_t seg_edges,
     return g->layouts.count(LayoutKey(R, light_limit(heavy_deg), seg_edges, pack ? 1 : 0)) != 0;
 }
 
+// The replica step's group width (lgW) for a sim with these light rows, or
+// -1: unit weights, constant shedding, fixed steps, at least four replicas,
+// neither rates nor compaction, and light rows of at most REPS_MAX_DEG edges
+// (counted in bytes).
+//  Below REPS_CHUNKS chunks a launch is one chain of latencies, which the
+//  variants' shorter one serves better (us per step, variant / replica step:
+//  regular d = 10, N = 3e4, R = 4, 1875 chunks 5.3 / 7.2; Erdos-Renyi 10, N =
+//  1e4, R = 16, 2500 chunks 8.5 / 8.9; N = 1e5, R = 8, 12500 chunks 14.7 /
+//  11.8; Barabasi-Albert 8, N = 6e4, R = 16, 15000 chunks 23.2 / 17.4).  With four
+//  replicas of a uniform graph a load brings only four bits and the LDS
+//  summary screens most edges (regular d = 10, N = 1e6: 37 / 55; on a
+//  Barabasi-Albert graph, which streams, 101 / 51).
+//  The widest group shares most work, the narrowest gives small sims more
+//  wavefronts: the widest that leaves REPS_GROUPS of them (Barabasi-Albert 4, N =
+//  3e5, R = 16: 4688 groups of 16 chunks 33.3 us, 9375 of 8 34.0, 18750 of 4
+//  38; Erdos-Renyi 10, N = 3e4, R = 64: 1875 / 3750 / 7500 groups 14.0 / 12.8 / 17).
+int replica_width(const fs_graph* g, const fs_sim_params& p, int lgR, int32_t limit)
+{
+    if (lgR < 2 || g->d_weights || p.shedding != FS_SHED_CONSTANT || p.adaptive || p.record_rates || p.compaction)
+        return -1;
+    if (std::min(limit, g->max_degree) > fsi::REPS_MAX_DEG) return -1;
+    const size_t chunks = (((size_t)g->n << lgR) + 63) / 64;
+    const bool uniform = g->min_degree == g->max_degree && g->max_degree <= fsi::UNIFORM_MAX_DEG;
+    if (chunks < fsi::REPS_CHUNKS || (uniform && lgR < 3)) return -1;
+    int w = std::min(lgR, 4);
+    while (w > 2 && (chunks >> w) < fsi::REPS_GROUPS) --w;
+    return w;
+}
+
+// Threads and workgroups of a sim's step launch in a variant, or (lgW >= 0)
+// of the replica step.
+void step_shape(const fs_sim* s, int mode, int lgW, uint32_t* tpb, uint32_t* G)
+{
+    const size_t chunks = ((size_t)s->g->n * (size_t)s->R + 63) / 64;
+    const bool stream = lgW >= 0 || mode == fsi::MODE_STREAM;
+    *tpb = stream ? fsi::STREAM_TPB : fsi::RESIDENT_TPB;
+    const size_t waves = lgW >= 0 ? (chunks + ((size_t)1 << lgW) - 1) >> lgW : chunks;
+    const size_t tiles = (waves + *tpb / 64 - 1) / (*tpb / 64); // workgroups with work
+    *G = (uint32_t)std::min<size_t>(tiles, stream ? fsi::max_step_grid(s->R) : s->cus);
+}
+
+// Gives the sim the launch shape of (mode, lgW).  Count partials are written
+// and reduced within one launch sequence: nothing of them outlives it.
+fs_status set_shape(fs_sim* s, int mode, int lgW)
+{
+    uint32_t tpb, G;
+    step_shape(s, mode, lgW, &tpb, &G);
+    if (G != s->G || !s->d_part) {
+        sim_free(s, s->d_part);
+        s->d_part = nullptr;
+        FS_HIP(sim_alloc(s, (void**)&s->d_part, (size_t)s->chunk * G * (size_t)s->R * 4 * sizeof(uint32_t)));
+    }
+    if (lgW >= 0 && !s->d_base) FS_HIP(sim_alloc(s, (void**)&s->d_base, (size_t)s->R * 4 * sizeof(uint32_t)));
+    if (lgW != s->lgW) s->base_stale = true;
+    s->mode = mode;
+    s->lgW = lgW;
+    s->tpb = tpb;
+    s->G = G;
+    s->args.part = s->d_part;
+    return FS_OK;
+}
+
+hipError_t refresh_base(fs_sim* s)
+{
+    if (s->lgW < 0 || !s->base_stale) return hipSuccess;
+    const hipError_t e = fsk::launch_count_all(s->storage, s->d_state, (uint32_t)s->g->n << s->lgR, s->lgR, s->d_base,
+                                               s->stream);
+    if (e == hipSuccess) s->base_stale = false;
+    return e;
+}
+
 // Whether a sim of these parameters may take packed columns: the
 // single-replica step of an unweighted graph (not age-dependent shedding
 // together with rate recording or compaction), unless the caller asks for
@@ -525,6 +597,17 @@ bool packing_allowed(const fs_graph* g, const fs_sim_params* p)
 {
     return p->columns == FS_COLUMNS_AUTO && std::max(p->n_replicas, 1) == 1 && g->d_weights == nullptr &&
            !(p->shedding != FS_SHED_CONSTANT && (p->record_rates || p->compaction));
+}
+
+// The replica count whose layout a sim of these parameters reads: its own,
+// or (replica step) its replica blocks per node.
+int32_t layout_replicas(const fs_graph* g, const fs_sim_params& p, int32_t heavy_deg)
+{
+    const int R = std::max(p.n_replicas, 1);
+    int lgR = 0;
+    while ((1 << lgR) < R) ++lgR;
+    const int w = replica_width(g, p, lgR, light_limit(heavy_deg));
+    return w < 0 ? R : R >> w;
 }
 
 size_t sim_footprint(fs_graph* g, const fs_sim_params* p)
@@ -540,7 +623,8 @@ size_t sim_footprint(fs_graph* g, const fs_sim_params* p)
     const int32_t hd = p->heavy_degree == 0 ? 64 : p->heavy_degree;
     const int32_t se = p->segment_edges == 0 ? 512 : p->segment_edges;
     const bool pk = packing_allowed(g, p);
-    if (!layout_cached(g, (int32_t)R, hd, se, pk)) {
+    const int32_t lr = layout_replicas(g, *p, hd);
+    if (!layout_cached(g, lr, hd, se, pk)) {
         b += (size_t)g->nnz * 4 * (g->d_weights ? 2 : 1);   // transposed light rows (+ weights)
         b += (size_t)g->n * 2 + ((size_t)g->n * R / 64 + 1) * 5; // degrees, chunk metadata
         b += (size_t)g->nnz / 64 * 16 + (size_t)g->n * 4;   // heavy segments (upper bound)
@@ -550,7 +634,7 @@ size_t sim_footprint(fs_graph* g, const fs_sim_params* p)
         // pushed pressure of binned rows: at most nnz / (hd + 1) rows
         const size_t hubs = std::min<size_t>((size_t)g->n, (size_t)g->nnz / ((size_t)hd + 1));
         b += 5 * hubs * R * 4;
-        if (!layout_cached(g, (int32_t)R, hd, se, pk)) b += ((size_t)g->n + 1) * 4 + (size_t)g->nnz * 4;
+        if (!layout_cached(g, lr, hd, se, pk)) b += ((size_t)g->n + 1) * 4 + (size_t)g->nnz * 4;
     }
     if (p->record_rates) b += units * 4;
     if (p->shedding != FS_SHED_CONSTANT) b += units * 2 * shed_bytes(p->storage);
@@ -573,6 +657,17 @@ hipError_t refresh_hubs(fs_sim* s, int64_t step)
     return fsk::launch_clear_u32(s->d_hub + 2 * (size_t)HU, 3 * (size_t)HU, s->stream);
 }
 
+hipError_t refresh_summary(fs_sim* s);
+
+// The step kernel of the sim's current configuration (nullptr: none).
+const void* step_fn(const fs_sim* s)
+{
+    if (s->lgW >= 0) return fsk::reps_kernel_fn(s->storage, s->lgW, false);
+    return fsk::step_kernel_fn(s->storage, s->g->d_weights != nullptr, s->mode, s->layout ? s->layout->udeg : -1,
+                               s->d_shed[0] != nullptr, s->d_rates != nullptr || s->d_act != nullptr, s->lgR,
+                               s->layout ? s->layout->pbits : 0);
+}
+
 // Points sim s at the layout of its graph for (R, heavy_deg, seg_edges),
 // building it on first use, and gives s its own heavy-segment partials.
 // Cached layouts no sim uses any more, other than this one, are released.
@@ -581,7 +676,9 @@ fs_status apply_bins(fs_sim* s, int32_t heavy_deg, int32_t seg_edges)
     fs_graph* g = s->g;
     if (seg_edges < 64 || seg_edges > (1 << 20)) return fail(FS_ERR_INVALID_ARG, "segment_edges must be in [64, 2^20]");
     const int32_t limit = light_limit(heavy_deg);
-    const LayoutKey key(s->R, limit, seg_edges, s->pack ? 1 : 0);
+    const int lgW = replica_width(g, s->p, s->lgR, limit);
+    const int32_t lr = lgW < 0 ? s->R : s->R >> lgW;
+    const LayoutKey key(lr, limit, seg_edges, s->pack ? 1 : 0);
     std::shared_ptr<Layout> L;
     {
         std::lock_guard<std::mutex> lk(g->layout_mu);
@@ -589,12 +686,15 @@ fs_status apply_bins(fs_sim* s, int32_t heavy_deg, int32_t seg_edges)
         if (it != g->layouts.end()) {
             L = it->second;
         } else {
-            fs_status st = build_layout(g, s->R, limit, seg_edges, s->pack, L);
+            fs_status st = build_layout(g, lr, limit, seg_edges, s->pack, L);
             if (st != FS_OK) return st;
             g->layouts[key] = L;
         }
     }
     drop_graph_exec(s);
+    const bool left_replica_step = s->lgW >= 0 && lgW < 0;
+    fs_status shst = set_shape(s, s->mode, lgW);
+    if (shst != FS_OK) return shst;
     sim_free(s, s->d_seg_part);
     s->d_seg_part = nullptr;
     sim_free(s, s->d_hub);
@@ -638,8 +738,8 @@ fs_status apply_bins(fs_sim* s, int32_t heavy_deg, int32_t seg_edges)
     s->args.orig_id = g->d_orig;
     s->args.udeg = L->udeg;
     s->args.pbits = L->pbits;
-    s->kfn = fsk::step_kernel_fn(s->storage, g->d_weights != nullptr, s->mode, L->udeg, s->d_shed[0] != nullptr,
-                                 s->d_rates != nullptr || s->d_act != nullptr, s->lgR, L->pbits);
+    if (left_replica_step) FS_HIP(refresh_summary(s)); // (the replica step keeps none)
+    s->kfn = step_fn(s);
     if (!s->kfn) return fail(FS_ERR_DEVICE, "no step kernel for this configuration");
     s->args.col_t = L->d_col_t;
     s->args.w_t = L->d_w_t;
@@ -675,7 +775,7 @@ uint32_t summary_grid(const fs_sim* s) { return (s->sum_words * 64u + WG - 1) / 
 // ctl->step must already hold the sim's step index).
 hipError_t refresh_summary(fs_sim* s)
 {
-    if (s->mode != fsi::MODE_SUMMARY) return hipSuccess;
+    if (s->mode != fsi::MODE_SUMMARY || s->lgW >= 0) return hipSuccess;
     fsi::SumArgs a = summary_args(s, 0);
     void* argv[] = {&a};
     return hipLaunchKernel(fsk::summary_kernel_fn(), dim3(summary_grid(s)), dim3(WG), argv, 0, s->stream);
@@ -738,7 +838,7 @@ void make_seq(fs_sim* s, uint32_t r, SeqArgs& q)
         for (uint32_t j = 0; j < r; ++j) q.heavy[j].step_off = j;
     }
     q.sum.clear();
-    if (s->mode == fsi::MODE_SUMMARY) {
+    if (s->mode == fsi::MODE_SUMMARY && s->lgW < 0) {
         q.sum.assign(r, summary_args(s, 1));
         for (uint32_t j = 0; j < r; ++j) q.sum[j].step_off = j;
     }
@@ -749,6 +849,7 @@ void make_seq(fs_sim* s, uint32_t r, SeqArgs& q)
     q.H = (uint32_t)s->H;
     q.r = r;
     q.hist = s->d_hist;
+    q.base = s->lgW >= 0 ? s->d_base : nullptr;
     q.live = s->d_live;
     q.nchunks = s->nchunks;
     q.rows = 64u >> s->lgR;
@@ -799,7 +900,7 @@ fs_status build_graph_exec(fs_sim* s, int b)
             if ((st = add(fsk::summary_kernel_fn(), dim3(summary_grid(s)), dim3(WG), sargv)) != FS_OK) return st;
         }
     }
-    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H};
+    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H, &q.base};
     if ((st = add(fsk::reduce_kernel_fn(), dim3(q.r), dim3(fsi::RED_TPB), rargv)) != FS_OK) return st;
     FS_HIP(hipGraphInstantiate(&s->exec, s->graph, nullptr, nullptr, 0));
     return FS_OK;
@@ -807,6 +908,7 @@ fs_status build_graph_exec(fs_sim* s, int b)
 
 fs_status launch_sequence(fs_sim* s, uint32_t r)
 {
+    FS_HIP(refresh_base(s));
     SeqArgs q;
     make_seq(s, r, q);
     if (s->d_act) {
@@ -830,7 +932,7 @@ fs_status launch_sequence(fs_sim* s, uint32_t r)
             FS_HIP(hipLaunchKernel(fsk::summary_kernel_fn(), dim3(summary_grid(s)), dim3(WG), sargv, 0, s->stream));
         }
     }
-    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H};
+    void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H, &q.base};
     FS_HIP(hipLaunchKernel(fsk::reduce_kernel_fn(), dim3(r), dim3(fsi::RED_TPB), rargv, 0, s->stream));
     return FS_OK;
 }
@@ -851,6 +953,7 @@ fs_status check_seed(const fs_sim* s, int32_t replica, int64_t count, const int6
 
 fs_status seed_staged(fs_sim* s, int32_t replica, const int64_t* d_nodes, int64_t count, int32_t compartment)
 {
+    s->base_stale = true;
     FS_HIP(fsk::launch_seed(s->storage, s->d_state, s->d_age, d_nodes, count, s->lgR, replica, compartment,
                             s->stream));
     FS_HIP(fsk::launch_rebuild_bits(s->storage, s->d_state, (uint32_t)(s->g->n * s->R),
@@ -872,37 +975,14 @@ fs_status apply_variant(fs_sim* s, int mode)
     if (mode == fsi::MODE_RESIDENT && units > fsi::RESIDENT_BITS)
         return fail(FS_ERR_INVALID_ARG, "the resident variant holds at most 2^20 units");
     if (mode == fsi::MODE_STREAM && s->p.adaptive) return fail(FS_ERR_INVALID_ARG, "adaptive sims keep an LDS variant");
-    const uint32_t tpb = mode == fsi::MODE_STREAM ? fsi::STREAM_TPB : fsi::RESIDENT_TPB;
-    const size_t chunks = (units + 63) / 64;
-    const size_t tiles = (chunks + tpb / 64 - 1) / (tpb / 64);
-    uint32_t G;
-    if (mode != fsi::MODE_STREAM) {
-        int cus = 0;
-        FS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device));
-        s->cus = (uint32_t)std::max(cus, 1);
-        G = (uint32_t)std::min<size_t>(tiles, s->cus);
-    } else {
-        G = (uint32_t)std::min<size_t>(tiles, fsi::max_step_grid(s->R));
-    }
     drop_graph_exec(s);
-    if (G != s->G) {
-        // count partials are written and reduced within one launch sequence:
-        // nothing of them outlives it
-        sim_free(s, s->d_part);
-        s->d_part = nullptr;
-        FS_HIP(sim_alloc(s, (void**)&s->d_part, (size_t)s->chunk * G * (size_t)s->R * 4 * sizeof(uint32_t)));
-    }
+    fs_status shst = set_shape(s, mode, s->lgW);
+    if (shst != FS_OK) return shst;
     if (mode == fsi::MODE_SUMMARY && !s->d_summary)
         FS_HIP(sim_alloc(s, (void**)&s->d_summary, ((size_t)s->sum_bits + 511) / 512 * 64));
-    s->mode = mode;
-    s->tpb = tpb;
-    s->G = G;
-    s->args.part = s->d_part;
     s->args.summary = (const uint32_t*)s->d_summary;
     const bool weighted = s->g->d_weights != nullptr, shed = s->d_shed[0] != nullptr;
-    s->kfn = fsk::step_kernel_fn(s->storage, weighted, mode, s->layout ? s->layout->udeg : -1, shed,
-                                 s->d_rates != nullptr || s->d_act != nullptr, s->lgR,
-                                 s->layout ? s->layout->pbits : 0);
+    s->kfn = step_fn(s);
     s->hfn = fsk::heavy_kernel_fn(weighted, shed, mode == fsi::MODE_RESIDENT);
     if (!s->kfn || !s->hfn) return fail(FS_ERR_DEVICE, "no step kernel for this configuration");
     FS_HIP(refresh_summary(s));
@@ -1034,7 +1114,7 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     }
     // candidates: the entry configuration first, then the other variants and bins
     std::vector<int> modes{s->mode};
-    if (tp.variants) {
+    if (tp.variants && s->lgW < 0) { // (the replica step is the same in every variant)
         for (int m : {fsi::MODE_RESIDENT, fsi::MODE_SUMMARY, fsi::MODE_STREAM}) {
             if (m == s->mode) continue;
             if (m == fsi::MODE_RESIDENT && units > fsi::RESIDENT_BITS) continue;
@@ -1094,6 +1174,7 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
                 best_mode = m;
                 best = c;
             }
+            s->base_stale = true;
             for (auto& b : bufs)
                 if (b.live && hipMemcpyAsync(b.live, b.copy.p, b.bytes, hipMemcpyDeviceToDevice, s->stream) != hipSuccess) {
                     st = fail(FS_ERR_DEVICE, "restore");
@@ -1104,6 +1185,7 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    s->base_stale = true;
     for (auto& b : bufs)
         if (b.live) (void)hipMemcpyAsync(b.live, b.copy.p, b.bytes, hipMemcpyDeviceToDevice, s->stream);
     FS_HIP(hipStreamSynchronize(s->stream));
@@ -1383,18 +1465,15 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
         s->sum_bits = (uint32_t)((words32 + ((size_t)1 << s->sum_shift) - 1) >> s->sum_shift);
     }
     s->sum_words = (s->sum_bits + 63) / 64;
-    s->tpb = s->mode == fsi::MODE_STREAM ? fsi::STREAM_TPB : fsi::RESIDENT_TPB;
     const size_t chunks = (units + 63) / 64;
-    const size_t tiles = (chunks + s->tpb / 64 - 1) / (s->tpb / 64); // workgroups with work
-    if (s->mode != fsi::MODE_STREAM) {
+    {
         int cus = 0;
         if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device)) != hipSuccess)
             return bad(e, "device attribute");
-        s->G = (uint32_t)std::min<size_t>(tiles, (size_t)std::max(cus, 1));
         s->cus = (uint32_t)std::max(cus, 1);
-    } else {
-        s->G = (uint32_t)std::min<size_t>(tiles, fsi::max_step_grid(R));
     }
+    s->lgW = replica_width(g, *p, s->lgR, light_limit(p->heavy_degree == 0 ? 64 : p->heavy_degree));
+    step_shape(s, s->mode, s->lgW, &s->tpb, &s->G);
     s->bit_words = (uint32_t)bitmap_words(units);
     s->nchunks = (uint32_t)chunks;
     s->live_bytes = (chunks + fsi::LIVE_TILE - 1) / fsi::LIVE_TILE * fsi::LIVE_TILE;
@@ -1411,6 +1490,7 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
         (e = sim_alloc(s, (void**)&s->d_ctl, sizeof(fsi::Ctl))) != hipSuccess ||
         (e = sim_alloc(s, (void**)&s->d_hist, hist_words * sizeof(uint32_t))) != hipSuccess ||
         (e = sim_alloc(s, (void**)&s->d_part, part_words * sizeof(uint32_t))) != hipSuccess ||
+        (s->lgW >= 0 && (e = sim_alloc(s, (void**)&s->d_base, (size_t)R * 4 * sizeof(uint32_t))) != hipSuccess) ||
         (e = sim_alloc(s, (void**)&s->d_rc_part, RC_GRID * 4 * sizeof(uint32_t))) != hipSuccess ||
         (e = sim_alloc(s, (void**)&s->d_cnt4, 4 * sizeof(uint32_t))) != hipSuccess ||
         (s->mode == fsi::MODE_SUMMARY &&
@@ -1505,8 +1585,7 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
         a.htab_len = fsi::HTAB_LEN;
         a.htab_inv = s->storage == 0 ? 1.0f / a.dt : 1.0f;
     }
-    s->kfn = fsk::step_kernel_fn(s->storage, g->d_weights != nullptr, s->mode, -1, shedding,
-                                 s->d_rates != nullptr || s->d_act != nullptr, s->lgR, 0);
+    s->kfn = step_fn(s);
     s->hfn = fsk::heavy_kernel_fn(g->d_weights != nullptr, shedding, s->mode == fsi::MODE_RESIDENT);
     s->pack = packing_allowed(g, p);
     if (!s->kfn || !s->hfn) {
@@ -1648,6 +1727,7 @@ fs_status fs_step(fs_sim* s, int64_t n_steps)
             fs_status st = build_graph_exec(s, b);
             if (st != FS_OK) return st;
         }
+        FS_HIP(refresh_base(s));
         for (int64_t r = 0; r < n_steps / b; ++r) FS_HIP(hipGraphLaunch(s->exec, s->stream));
         rem = n_steps % b;
     }
@@ -1804,6 +1884,7 @@ fs_status fs_set_state(fs_sim* s, int32_t replica, const int32_t* state, const f
     state = to_internal(s->g, state, st_tmp);
     age_in = s->storage == FS_STORAGE_FP32 ? (const void*)to_internal(s->g, age_days, ad_tmp)
                                            : (const void*)to_internal(s->g, age_steps, as_tmp);
+    s->base_stale = true;
     StreamBuf ds(s->stream); StreamBuf da(s->stream);
     FS_HIP(hipMallocAsync(&ds.p, n * sizeof(int32_t), s->stream));
     FS_HIP(hipMallocAsync(&da.p, n * age_bytes(s->storage), s->stream));
