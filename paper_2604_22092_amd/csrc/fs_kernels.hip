@@ -200,17 +200,19 @@ __global__ __launch_bounds__(WG) void recount_kernel(const void* state_v, int32_
     }
 }
 
-// Writes one replica's contiguous state/age into the interleaved layout.
+// Writes one replica's contiguous states and ages (caller's node order) into
+// the interleaved internal layout.
 template <int STORAGE>
-__global__ void put_replica_kernel(void* state_v, void* age_v, const int32_t* src_state, const void* src_age,
-                                   int32_t n, int32_t lgR, int32_t replica)
+__global__ void put_replica_kernel(void* state_v, void* age_v, const uint8_t* src_state, const void* src_age,
+                                   const int32_t* orig, int32_t n, int32_t lgR, int32_t replica)
 {
     using S = Store<STORAGE>;
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (uint32_t)n) return;
     const size_t u = ((size_t)i << lgR) + replica;
-    ((typename S::state_t*)state_v)[u] = (typename S::state_t)src_state[i];
-    ((typename S::age_t*)age_v)[u] = ((const typename S::age_t*)src_age)[i];
+    const uint32_t c = orig ? (uint32_t)orig[i] : i;
+    ((typename S::state_t*)state_v)[u] = (typename S::state_t)src_state[c];
+    ((typename S::age_t*)age_v)[u] = ((const typename S::age_t*)src_age)[c];
 }
 
 // Rebuilds an infectivity bitmap from the states: one 64-bit word per wave.
@@ -228,23 +230,24 @@ __global__ __launch_bounds__(WG) void rebuild_bits_kernel(const void* state_v, u
 }
 
 template <int STORAGE>
-__global__ void get_replica_kernel(const void* state_v, const void* age_v, int32_t* dst_state,
-                                   void* dst_age, int32_t n, int32_t lgR, int32_t replica)
+__global__ void get_replica_kernel(const void* state_v, const void* age_v, uint8_t* dst_state, void* dst_age,
+                                   const int32_t* orig, int32_t n, int32_t lgR, int32_t replica)
 {
     using S = Store<STORAGE>;
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (uint32_t)n) return;
     const size_t u = ((size_t)i << lgR) + replica;
-    dst_state[i] = (int32_t)((const typename S::state_t*)state_v)[u];
-    ((typename S::age_t*)dst_age)[i] = ((const typename S::age_t*)age_v)[u];
+    const uint32_t c = orig ? (uint32_t)orig[i] : i;
+    dst_state[c] = (uint8_t)((const typename S::state_t*)state_v)[u];
+    ((typename S::age_t*)dst_age)[c] = ((const typename S::age_t*)age_v)[u];
 }
 
-template <int STORAGE>
-__global__ void get_rates_kernel(const float* rates, float* dst, int32_t n, int32_t lgR, int32_t replica)
+__global__ void get_rates_kernel(const float* rates, float* dst, const int32_t* orig, int32_t n, int32_t lgR,
+                                 int32_t replica)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (uint32_t)n) return;
-    dst[i] = rates[((size_t)i << lgR) + replica];
+    dst[orig ? (uint32_t)orig[i] : i] = rates[((size_t)i << lgR) + replica];
 }
 
 // Seeds listed nodes of one replica (or all replicas) into `comp` at age 0.
@@ -471,17 +474,17 @@ const void* heavy_batch_kernel_fn(bool weighted)
 }
 const void* reduce_batch_kernel_fn() { return (const void*)&reduce_batch_kernel; }
 
-hipError_t launch_put_replica(int storage, void* state, void* age, const int32_t* src_state, const void* src_age,
-                              int32_t n, int32_t lgR, int32_t replica, hipStream_t s)
+hipError_t launch_put_replica(int storage, void* state, void* age, const uint8_t* src_state, const void* src_age,
+                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
     unsigned g = grid_for((size_t)n, 256);
     if (storage == 0)
-        hipLaunchKernelGGL(put_replica_kernel<0>, dim3(g), dim3(256), 0, s, state, age, src_state, src_age, n, lgR,
-                           replica);
+        hipLaunchKernelGGL(put_replica_kernel<0>, dim3(g), dim3(256), 0, s, state, age, src_state, src_age, orig, n,
+                           lgR, replica);
     else
-        hipLaunchKernelGGL(put_replica_kernel<1>, dim3(g), dim3(256), 0, s, state, age, src_state, src_age, n, lgR,
-                           replica);
+        hipLaunchKernelGGL(put_replica_kernel<1>, dim3(g), dim3(256), 0, s, state, age, src_state, src_age, orig, n,
+                           lgR, replica);
     return hipGetLastError();
 }
 
@@ -497,26 +500,26 @@ hipError_t launch_rebuild_bits(int storage, const void* state, uint32_t total, u
     return hipGetLastError();
 }
 
-hipError_t launch_get_replica(int storage, const void* state, const void* age, int32_t* dst_state,
-                              void* dst_age, int32_t n, int32_t lgR, int32_t replica, hipStream_t s)
+hipError_t launch_get_replica(int storage, const void* state, const void* age, uint8_t* dst_state, void* dst_age,
+                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
     unsigned g = grid_for((size_t)n, 256);
     if (storage == 0)
-        hipLaunchKernelGGL(get_replica_kernel<0>, dim3(g), dim3(256), 0, s, state, age, dst_state, dst_age,
-                           n, lgR, replica);
+        hipLaunchKernelGGL(get_replica_kernel<0>, dim3(g), dim3(256), 0, s, state, age, dst_state, dst_age, orig, n,
+                           lgR, replica);
     else
-        hipLaunchKernelGGL(get_replica_kernel<1>, dim3(g), dim3(256), 0, s, state, age, dst_state, dst_age,
-                           n, lgR, replica);
+        hipLaunchKernelGGL(get_replica_kernel<1>, dim3(g), dim3(256), 0, s, state, age, dst_state, dst_age, orig, n,
+                           lgR, replica);
     return hipGetLastError();
 }
 
-hipError_t launch_get_rates(const float* rates, float* dst, int32_t n, int32_t lgR, int32_t replica,
-                            hipStream_t s)
+hipError_t launch_get_rates(const float* rates, float* dst, const int32_t* orig, int32_t n, int32_t lgR,
+                            int32_t replica, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(get_rates_kernel<0>, dim3(grid_for((size_t)n, 256)), dim3(256), 0, s, rates, dst, n,
-                       lgR, replica);
+    hipLaunchKernelGGL(get_rates_kernel, dim3(grid_for((size_t)n, 256)), dim3(256), 0, s, rates, dst, orig, n, lgR,
+                       replica);
     return hipGetLastError();
 }
 

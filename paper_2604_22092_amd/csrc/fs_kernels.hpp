@@ -74,14 +74,17 @@ const void* heavy_batch_kernel_fn(bool weighted);
 // reduce_batch_kernel(const RedArgs* table): grid (r, members), RED_TPB threads;
 // advances every member's step index by r
 const void* reduce_batch_kernel_fn();
-hipError_t launch_put_replica(int storage, void* state, void* age, const int32_t* src_state, const void* src_age,
-                              int32_t n, int32_t lgR, int32_t replica, hipStream_t s);
+// One replica's states (bytes) and ages between the caller's node order and
+// the interleaved internal layout; orig: internal -> caller's id, nullptr for
+// the identity.
+hipError_t launch_put_replica(int storage, void* state, void* age, const uint8_t* src_state, const void* src_age,
+                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, hipStream_t s);
 hipError_t launch_rebuild_bits(int storage, const void* state, uint32_t total, unsigned long long* bits,
                                uint32_t words, hipStream_t s);
-hipError_t launch_get_replica(int storage, const void* state, const void* age, int32_t* dst_state,
-                              void* dst_age, int32_t n, int32_t lgR, int32_t replica, hipStream_t s);
-hipError_t launch_get_rates(const float* rates, float* dst, int32_t n, int32_t lgR, int32_t replica,
-                            hipStream_t s);
+hipError_t launch_get_replica(int storage, const void* state, const void* age, uint8_t* dst_state, void* dst_age,
+                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, hipStream_t s);
+hipError_t launch_get_rates(const float* rates, float* dst, const int32_t* orig, int32_t n, int32_t lgR,
+                            int32_t replica, hipStream_t s);
 hipError_t launch_seed(int storage, void* state, void* age, const int64_t* nodes, int64_t count, int32_t lgR,
                        int32_t replica, int32_t comp, hipStream_t s);
 hipError_t launch_clear_u32(uint32_t* p, size_t n, hipStream_t s);

@@ -325,10 +325,22 @@ __global__ void mk_seed_kernel(uint8_t* state, const int64_t* nodes, int64_t cou
     if (j < count) state[nodes[j]] = (uint8_t)comp;
 }
 
-__global__ void mk_put_kernel(uint8_t* state, const int32_t* src, uint32_t n)
+// States (and influences) between the caller's node order and the internal
+// one (orig: internal -> caller's id, nullptr for the identity).
+__global__ void mk_put_kernel(uint8_t* state, const uint8_t* src, const int32_t* orig, uint32_t n)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) state[i] = (uint8_t)src[i];
+    if (i < n) state[i] = src[orig ? (uint32_t)orig[i] : i];
+}
+
+__global__ void mk_get_kernel(const uint8_t* state, const int32_t* infl, const int32_t* orig, uint32_t n,
+                              uint8_t* dst_state, int32_t* dst_infl)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t c = orig ? (uint32_t)orig[i] : i;
+    dst_state[c] = state[i];
+    dst_infl[c] = infl[i];
 }
 
 __global__ void mk_clear_kernel(double* elapsed, double value)
@@ -671,19 +683,17 @@ fs_status fs_markov_set_state(fs_markov* m, const int32_t* state, int64_t step_i
     if (step_index < -1) return fail(FS_ERR_INVALID_ARG, "step_index must be >= -1");
     if (!(elapsed >= 0.0) || !std::isfinite(elapsed)) return fail(FS_ERR_INVALID_ARG, "elapsed must be finite and >= 0");
     const size_t n = (size_t)m->g->n;
-    std::vector<int32_t> st(n);
-    for (size_t i = 0; i < n; ++i) {
-        const int32_t v = m->g->h_orig.empty() ? state[i] : state[(size_t)m->g->h_orig[i]];
-        if (v < 0 || v > 3) return fail(FS_ERR_INVALID_ARG, "state values must lie in [0, 3]");
-        st[i] = v;
-    }
     DeviceGuard dg(m->device);
     const int64_t new_step = step_index >= 0 ? step_index : m->step;
     StreamBuf tmp(m->stream);
-    FS_HIP(hipMallocAsync(&tmp.p, n * 4, m->stream));
-    FS_HIP(hipMemcpyAsync(tmp.p, st.data(), n * 4, hipMemcpyHostToDevice, m->stream));
+    FS_HIP(hipMallocAsync(&tmp.p, n, m->stream));
+    bool bad_state = false, bad_age = false;
+    const fs_status st = copy_in(m->device, m->stream, n, state, (uint8_t*)tmp.p, nullptr, nullptr, 0, false, &bad_state,
+                                 &bad_age);
+    if (bad_state) return fail(FS_ERR_INVALID_ARG, "state values must lie in [0, 3]");
+    if (st != FS_OK) return st;
     hipLaunchKernelGGL(fsm::mk_put_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->stream, m->d_state,
-                       (const int32_t*)tmp.p, (uint32_t)n);
+                       (const uint8_t*)tmp.p, m->g->h_orig.empty() ? (const int32_t*)nullptr : m->g->d_orig, (uint32_t)n);
     FS_HIP(hipGetLastError());
     hipLaunchKernelGGL(fsm::mk_clear_kernel, dim3(1), dim3(64), 0, m->stream, m->d_elapsed, elapsed);
     FS_HIP(hipGetLastError());
@@ -738,18 +748,19 @@ fs_status fs_markov_get_state(fs_markov* m, int32_t* state, int32_t* influence, 
     if (!m) return fail(FS_ERR_INVALID_ARG, "engine is NULL");
     DeviceGuard dg(m->device);
     const size_t n = (size_t)m->g->n;
-    std::vector<uint8_t> st(n);
-    std::vector<int32_t> inf(n);
     double el = 0.0;
-    FS_HIP(hipMemcpyAsync(st.data(), m->d_state, n, hipMemcpyDeviceToHost, m->stream));
-    FS_HIP(hipMemcpyAsync(inf.data(), m->d_infl, n * 4, hipMemcpyDeviceToHost, m->stream));
+    StreamBuf tmp(m->stream);
+    FS_HIP(hipMallocAsync(&tmp.p, n * 5, m->stream));
+    uint8_t* d_state = (uint8_t*)tmp.p + n * 4;
+    hipLaunchKernelGGL(fsm::mk_get_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->stream,
+                       (const uint8_t*)m->d_state, (const int32_t*)m->d_infl,
+                       m->g->h_orig.empty() ? (const int32_t*)nullptr : m->g->d_orig, (uint32_t)n, d_state,
+                       (int32_t*)tmp.p);
+    FS_HIP(hipGetLastError());
+    const fs_status st = copy_out(m->device, m->stream, n, d_state, state, tmp.p, influence, 4);
+    if (st != FS_OK) return st;
     FS_HIP(hipMemcpyAsync(&el, m->d_elapsed, 8, hipMemcpyDeviceToHost, m->stream));
     FS_HIP(hipStreamSynchronize(m->stream));
-    for (size_t i = 0; i < n; ++i) {
-        const size_t c = m->g->h_orig.empty() ? i : (size_t)m->g->h_orig[i];
-        if (state) state[c] = st[i];
-        if (influence) influence[c] = inf[i];
-    }
     if (step_index) *step_index = m->step;
     if (elapsed) *elapsed = el;
     return FS_OK;

@@ -130,23 +130,8 @@ void sim_free(fs_sim* s, void* p)
     }
 }
 
-// Per-node arrays between the caller's node order and a graph's internal
-// order (no copy when the graph keeps the caller's order).
-template <class T>
-const T* to_internal(const fs_graph* g, const T* in, std::vector<T>& tmp)
-{
-    if (g->h_orig.empty()) return in;
-    tmp.resize(g->h_orig.size());
-    for (size_t j = 0; j < tmp.size(); ++j) tmp[j] = in[g->h_orig[j]];
-    return tmp.data();
-}
-
-template <class T>
-void to_caller(const fs_graph* g, const T* in, T* out)
-{
-    for (size_t j = 0; j < g->h_orig.size(); ++j) out[g->h_orig[j]] = in[j];
-}
-
+// The order of a graph's internal nodes on the device (nullptr: the caller's).
+const int32_t* order_of(const fs_graph* g) { return g->h_orig.empty() ? nullptr : g->d_orig; }
 
 void split(double v, float& hi, float& lo)
 {
@@ -1338,6 +1323,7 @@ fs_status fs_graph_create(int64_t n, const int32_t* row_ptr, const int32_t* col_
          (e = hipMemcpy(g->d_weights, g->h_weights.data(), sizeof(float) * (size_t)nnz, hipMemcpyHostToDevice)) !=
              hipSuccess))
         return cleanup(fail(FS_ERR_DEVICE, std::string("upload: ") + hipGetErrorString(e)));
+    graph_opened();
     *out = g;
     return FS_OK;
     FS_GUARD_END
@@ -1356,6 +1342,7 @@ fs_status fs_graph_destroy(fs_graph* g)
     dev_free(g->d_out_ptr);
     dev_free(g->d_out_ind);
     delete g;
+    graph_closed();
     return FS_OK;
     FS_GUARD_END
 }
@@ -1787,15 +1774,8 @@ fs_status fs_history(fs_sim* s, int32_t replica, int64_t first_step, int64_t n, 
         return fail(FS_ERR_INVALID_ARG, "requested steps are not in the kept history [" + std::to_string(lo) +
                                             ", " + std::to_string(s->step) + ")");
     DeviceGuard dg(s->device);
-    const size_t row = (size_t)s->R * 4;
-    std::vector<uint32_t> h((size_t)s->H * row);
-    FS_HIP(hipMemcpyAsync(h.data(), s->d_hist, h.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s->stream));
-    FS_HIP(hipStreamSynchronize(s->stream));
-    for (int64_t j = 0; j < n; ++j) {
-        const size_t slot = (size_t)((first_step + j) % s->H);
-        for (int c = 0; c < 4; ++c) out[4 * j + c] = (int64_t)h[slot * row + (size_t)replica * 4 + c];
-    }
-    return FS_OK;
+    return copy_history(s->device, s->stream, s->d_hist, (uint32_t)s->R, (uint32_t)replica, (uint64_t)first_step,
+                        (uint32_t)s->H, (size_t)n, out);
     FS_GUARD_END
 }
 
@@ -1833,25 +1813,22 @@ fs_status fs_get_state(fs_sim* s, int32_t replica, int32_t* state, float* age_da
     if (!age_out || (s->storage == FS_STORAGE_FP32 ? age_steps != nullptr : age_days != nullptr))
         return fail(FS_ERR_INVALID_ARG, "pass exactly the age array of the sim's storage");
     DeviceGuard dg(s->device);
-    const size_t n = (size_t)s->g->n;
-    StreamBuf ds(s->stream); StreamBuf da(s->stream);
-    FS_HIP(hipMallocAsync(&ds.p, n * sizeof(int32_t), s->stream));
-    FS_HIP(hipMallocAsync(&da.p, n * age_bytes(s->storage), s->stream));
-    FS_HIP(fsk::launch_get_replica(s->storage, s->d_state, s->d_age, (int32_t*)ds.p, da.p, (int32_t)n, s->lgR,
-                                   replica, s->stream));
-    const bool reorder = !s->g->h_orig.empty();
-    std::vector<int32_t> st_int(reorder ? n : 0);
-    std::vector<uint8_t> age_int(reorder ? n * age_bytes(s->storage) : 0);
-    FS_HIP(hipMemcpyAsync(reorder ? (void*)st_int.data() : (void*)state, ds.p, n * sizeof(int32_t),
-                          hipMemcpyDeviceToHost, s->stream));
-    FS_HIP(hipMemcpyAsync(reorder ? (void*)age_int.data() : age_out, da.p, n * age_bytes(s->storage),
-                          hipMemcpyDeviceToHost, s->stream));
-    FS_HIP(hipStreamSynchronize(s->stream));
-    if (reorder) {
-        to_caller(s->g, st_int.data(), state);
-        if (s->storage == FS_STORAGE_FP32) to_caller(s->g, (const float*)age_int.data(), age_days);
-        else to_caller(s->g, (const uint16_t*)age_int.data(), age_steps);
+    const size_t n = (size_t)s->g->n, ab = age_bytes(s->storage);
+    auto read = [&](uint8_t* states, void* ages) {
+        return fsk::launch_get_replica(s->storage, s->d_state, s->d_age, states, ages, order_of(s->g), (int32_t)n,
+                                       s->lgR, replica, s->stream);
+    };
+    if (reads_direct(s->g)) {
+        st = read_direct(s->device, s->stream, n, ab, read, state, age_out);
+    } else {
+        // the replica in the caller's order: ages, then states as bytes
+        StreamBuf tmp(s->stream);
+        FS_HIP(hipMallocAsync(&tmp.p, n * (ab + 1), s->stream));
+        uint8_t* d_state = (uint8_t*)tmp.p + n * ab;
+        FS_HIP(read(d_state, tmp.p));
+        st = copy_out(s->device, s->stream, n, d_state, state, tmp.p, age_out, ab);
     }
+    if (st != FS_OK) return st;
     if (step_index) *step_index = s->step;
     return FS_OK;
     FS_GUARD_END
@@ -1868,29 +1845,21 @@ fs_status fs_set_state(fs_sim* s, int32_t replica, const int32_t* state, const f
     if (!age_in || (s->storage == FS_STORAGE_FP32 ? age_steps != nullptr : age_days != nullptr))
         return fail(FS_ERR_INVALID_ARG, "pass exactly the age array of the sim's storage");
     if (step_index < -1) return fail(FS_ERR_INVALID_ARG, "step_index must be >= -1");
-    const size_t n = (size_t)s->g->n;
-    for (size_t i = 0; i < n; ++i)
-        if (state[i] < 0 || state[i] > 3) return fail(FS_ERR_INVALID_ARG, "state values must lie in [0, 3]");
-    if (s->storage == FS_STORAGE_FP32)
-        for (size_t i = 0; i < n; ++i)
-            if (!(age_days[i] >= 0.0f) || !std::isfinite(age_days[i]))
-                return fail(FS_ERR_INVALID_ARG, "ages must be finite and >= 0");
+    const size_t n = (size_t)s->g->n, ab = age_bytes(s->storage);
     DeviceGuard dg(s->device);
     const int64_t new_step = step_index >= 0 ? step_index : s->step;
     const size_t units = n * (size_t)s->R;
-    std::vector<int32_t> st_tmp;
-    std::vector<float> ad_tmp;
-    std::vector<uint16_t> as_tmp;
-    state = to_internal(s->g, state, st_tmp);
-    age_in = s->storage == FS_STORAGE_FP32 ? (const void*)to_internal(s->g, age_days, ad_tmp)
-                                           : (const void*)to_internal(s->g, age_steps, as_tmp);
+    StreamBuf tmp(s->stream);
+    FS_HIP(hipMallocAsync(&tmp.p, n * (ab + 1), s->stream));
+    uint8_t* d_state = (uint8_t*)tmp.p + n * ab;
+    bool bad_state = false, bad_age = false;
+    st = copy_in(s->device, s->stream, n, state, d_state, age_in, tmp.p, ab, s->storage == FS_STORAGE_FP32, &bad_state,
+                 &bad_age);
+    if (bad_state) return fail(FS_ERR_INVALID_ARG, "state values must lie in [0, 3]");
+    if (bad_age) return fail(FS_ERR_INVALID_ARG, "ages must be finite and >= 0");
+    if (st != FS_OK) return st;
     s->base_stale = true;
-    StreamBuf ds(s->stream); StreamBuf da(s->stream);
-    FS_HIP(hipMallocAsync(&ds.p, n * sizeof(int32_t), s->stream));
-    FS_HIP(hipMallocAsync(&da.p, n * age_bytes(s->storage), s->stream));
-    FS_HIP(hipMemcpyAsync(ds.p, state, n * sizeof(int32_t), hipMemcpyHostToDevice, s->stream));
-    FS_HIP(hipMemcpyAsync(da.p, age_in, n * age_bytes(s->storage), hipMemcpyHostToDevice, s->stream));
-    FS_HIP(fsk::launch_put_replica(s->storage, s->d_state, s->d_age, (const int32_t*)ds.p, da.p, (int32_t)n, s->lgR,
+    FS_HIP(fsk::launch_put_replica(s->storage, s->d_state, s->d_age, d_state, tmp.p, order_of(s->g), (int32_t)n, s->lgR,
                                    replica, s->stream));
     FS_HIP(fsk::launch_rebuild_bits(s->storage, s->d_state, (uint32_t)units,
                                     (unsigned long long*)s->d_iota[new_step & 1], s->bit_words, s->stream));
@@ -1918,13 +1887,8 @@ fs_status fs_get_rates(fs_sim* s, int32_t replica, float* out)
     const size_t n = (size_t)s->g->n;
     StreamBuf d(s->stream);
     FS_HIP(hipMallocAsync(&d.p, n * sizeof(float), s->stream));
-    FS_HIP(fsk::launch_get_rates(s->d_rates, (float*)d.p, (int32_t)n, s->lgR, replica, s->stream));
-    const bool reorder = !s->g->h_orig.empty();
-    std::vector<float> r_int(reorder ? n : 0);
-    FS_HIP(hipMemcpyAsync(reorder ? r_int.data() : out, d.p, n * sizeof(float), hipMemcpyDeviceToHost, s->stream));
-    FS_HIP(hipStreamSynchronize(s->stream));
-    if (reorder) to_caller(s->g, r_int.data(), out);
-    return FS_OK;
+    FS_HIP(fsk::launch_get_rates(s->d_rates, (float*)d.p, order_of(s->g), (int32_t)n, s->lgR, replica, s->stream));
+    return copy_out(s->device, s->stream, n, nullptr, nullptr, d.p, out, sizeof(float));
     FS_GUARD_END
 }
 

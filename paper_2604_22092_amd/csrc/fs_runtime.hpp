@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -219,6 +220,29 @@ size_t sim_footprint(fs_graph* g, const fs_sim_params* p);
 // d_nodes (synchronises the sim's stream, so d_nodes may be reused after).
 fs_status check_seed(const fs_sim* s, int32_t replica, int64_t count, const int64_t* nodes, int32_t compartment);
 fs_status seed_staged(fs_sim* s, int32_t replica, const int64_t* d_nodes, int64_t count, int32_t compartment);
+// Host transfers (fs_transfer.hip).  Each returns when its arrays are done.
+// copy_out: n states (bytes) and payloads (pay_bytes <= 4 each) from device
+// memory into the caller's arrays; either may be NULL.
+// reads_direct / read_direct: a graph of one piece in the caller's order, whose
+// kernel (queued by put on `stream`) writes the bytes and payloads straight
+// into a pinned buffer: no staging and no copy.
+// copy_in: the other way, with the checks of a state load: *bad_state when a
+// state lies outside [0, 3], *bad_age (float_ages) when an age is not finite
+// or negative; the device copies are then incomplete.
+// copy_history: the counts of one replica of ring rows first_step ..
+// first_step + n - 1 (modulo H).
+// graph_opened / graph_closed bound the life of the pinned buffers.
+fs_status copy_out(int device, hipStream_t stream, size_t n, const uint8_t* d_state, int32_t* state, const void* d_pay,
+                   void* pay, size_t pay_bytes);
+bool reads_direct(const fs_graph* g);
+fs_status read_direct(int device, hipStream_t stream, size_t n, size_t pay_bytes,
+                      const std::function<hipError_t(uint8_t*, void*)>& put, int32_t* state, void* pay);
+fs_status copy_in(int device, hipStream_t stream, size_t n, const int32_t* state, uint8_t* d_state, const void* pay,
+                  void* d_pay, size_t pay_bytes, bool float_ages, bool* bad_state, bool* bad_age);
+fs_status copy_history(int device, hipStream_t stream, const uint32_t* d_hist, uint32_t R, uint32_t replica,
+                       uint64_t first_step, uint32_t H, size_t n, int64_t* out);
+void graph_opened();
+void graph_closed();
 // Puts a sim whose layout has packed columns on the graph's layout with
 // 32-bit columns (the batch kernel reads only those); the sim's stream must
 // be idle.  Results do not change.
