@@ -259,4 +259,22 @@ __device__ __forceinline__ float step_uniform(uint32_t node, uint32_t step, uint
     return (float)(w.x >> 8) * 0x1p-24f;
 }
 
+// Whether u < 1 - exp(-y) for the comparison the step makes in FP32
+// (u < -expm1f(-y)).  The Taylor bounds y - y^2/2 + y^3/6 - y^4/24 <= 1 -
+// exp(-y) <= y - y^2/2 + y^3/6, widened by 1e-6 y (many times the rounding of
+// expm1f and of the bounds for y <= 1), decide all but about y^4/24 of the
+// draws; only a wavefront holding one of those evaluates expm1f.
+__device__ __forceinline__ bool bernoulli(float u, float y)
+{
+    const float up = y * __builtin_fmaf(-y, __builtin_fmaf(y, -1.0f / 6.0f, 0.5f), 1.0f);
+    const float m = 1e-6f * y;
+    const float y2 = y * y;
+    const bool yes = u < up - __builtin_fmaf(y2 * y2, 1.0f / 24.0f, m);
+    const bool no = u >= up + m;
+    const bool sure = y <= 1.0f && (yes || no);
+    bool fire = yes;
+    if (!sure) fire = u < -expm1f(-y);
+    return fire;
+}
+
 } // namespace fsd

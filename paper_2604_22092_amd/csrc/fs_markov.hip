@@ -3,28 +3,35 @@
 //
 // Rates are piecewise constant: S nodes beta * I_i (I_i: infectious
 // in-neighbours, unit weights), E nodes sigma, I nodes gamma, R nodes 0.
-// One step is three launches, all inside a captured graph:
-//   draw   (dense): one wavefront per workgroup folds the per-workgroup rate
-//          partials of the previous launch into Lambda and max lambda (exact integers),
-//          takes tau = min(theta N / Lambda, p_max / max lambda, tau_max),
-//          draws every node with a positive rate and applies the transitions;
-//          a node whose infectiousness changed is appended to its
-//          workgroup's event region (no global counter);
-//   push   (sparse, Inertial Mode): when the step's events are few, each
-//          event adds +-1 to the influence of its out-neighbours (integer
-//          atomics on the outgoing CSR: exact and order-independent), the
-//          events spread over every lane of the grid; otherwise it exits.
-//          Without I -> S (SEIR, SIR) only susceptible targets are updated:
-//          no other node reads its influence again;
-//   rates  (dense): when the events were many (Control Mode) it recounts
-//          every influence from the incoming CSR, then writes per-workgroup
-//          (sum of S influences, max S influence, #E, #I) for the next draw;
-//          after a step without transitions it keeps the old partials.
+// One step is two launches, inside a captured graph:
+//   step   (dense, then sparse): one wavefront per workgroup folds the rate
+//          partials of the previous launch into Lambda and max lambda (exact
+//          integers) and takes tau = min(theta N / Lambda, p_max / max lambda,
+//          tau_max) while the workgroup's states and influences are on their
+//          way; every node with a positive rate draws and applies its
+//          transition; then (Inertial Mode) each node whose infectiousness
+//          changed adds +-1 to the pending influence of its out-neighbours
+//          (integer atomics: exact and order-independent).  Pending, because
+//          other workgroups still read the influences of this step.  Without
+//          I -> S (SEIR, SIR) only susceptible targets are updated: no other
+//          node reads its influence again;
+//   rates  (dense): adds the pending changes to the influences, or (Control
+//          Mode: many events in the step) recounts every influence from the
+//          incoming CSR, and writes per-workgroup partials (sum of S
+//          influences, max S influence, #E, #I) and counts; after a step
+//          without transitions it keeps the old ones.
 // Both modes give the same integer influences on every node that can still
 // read them (every susceptible node; every node under SIS), so results do not
 // depend on which ran.  Per-step counts, tau and event totals go to rings on the
 // device; a launch sequence ends with the count reduce, which also advances
 // the step index.
+//
+// What bounds it is latency: a step's dense arrays are 9 MB at N = 1e6 (2 us),
+// and its chain is two launches, the tau fold, the draws, and list -> target ->
+// state -> atomic.  Draws, pushes and rates as three launches with one lane per
+// node and one per event took 8.1 + 9.7 + 4.8 us (Erdos-Renyi d = 8, SIR, 600
+// steps); four nodes per lane loaded at once, draws packed and eight lanes per
+// event take 7.8 + 4.2 us (the whole run 14.3 -> 7.7 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,9 +47,13 @@ namespace fsm {
 
 using namespace fsi;
 
-constexpr int MTPB = 1024; // threads per workgroup of the dense kernels
-constexpr int PTPB = 256;  // threads per workgroup of the push kernel
+constexpr uint32_t MTPB = 1024;  // most threads per workgroup
+constexpr uint32_t NPL = 4;      // consecutive nodes per lane
+constexpr uint32_t MAX_REGIONS = 1024;
 constexpr uint32_t EV_LEAVE = 0x80000000u;
+// fired[] of a workgroup that left its pushes out (many events): the rates
+// launch recounts.
+constexpr uint32_t SKIPPED = 0x80000000u;
 
 struct MkArgs {
     uint8_t* state;
@@ -52,11 +63,11 @@ struct MkArgs {
     const int32_t* out_ptr; // outgoing CSR (internal order)
     const int32_t* out_ind;
     const int32_t* orig_id; // caller's id of each node: the draws are keyed by it
-    uint32_t* events;       // [G][span]: node | EV_LEAVE when it stopped being infectious
-    uint32_t* ev_cnt;       // [G] events of the current step per region
-    uint32_t* fired;        // [G] transitions of the current step per region (events or not);
-                            // fired[G] receives their total (written by the push launch)
+    int32_t* pending;       // influence changes of the current step, zero between steps
+    uint32_t* ev_cnt;       // [G] events of the current step per workgroup
+    uint32_t* fired;        // [G] transitions of the current step (events or not) | SKIPPED
     uint4* rpart;           // [G]: (sum of S influences, max S influence, #E, #I)
+    uint4* wcnt;            // [G]: counts after the last step
     uint32_t* part;         // count partials [slot][G][4]
     float* tau_hist;        // [H]
     uint32_t* ev_hist;      // [H]
@@ -69,6 +80,7 @@ struct MkArgs {
     double theta, p_max, tau_max;
     uint32_t key0, key1;
     uint32_t inertial_max;  // events per step up to which pushes update the influence
+    uint32_t wg_max;        // events of one workgroup up to which it pushes
     int32_t force_control;  // rates launch after a state change: recount everything
 };
 
@@ -80,13 +92,28 @@ __device__ __forceinline__ int next_state(int model, int x)
     return x;
 }
 
+// Sum (or maximum) of v over the wavefront, wave-uniform: lane-crossing adds
+// within rows of 16, then across rows (a shuffle would go through LDS, and the
+// folds sit on the launches' critical path).
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_fold(uint32_t v)
+{
+    auto op = [](uint32_t x, uint32_t y) { return MAX ? max(x, y) : x + y; };
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false)); // row_shr:1
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false)); // row_shr:2
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false)); // row_shr:4
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false)); // row_shr:8
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false)); // row_bcast:15
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false)); // row_bcast:31
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // tau of Algorithm "Markovian Engine" from the per-workgroup partials of the
-// rates launch (every wave folds them in the same order, so every wave gets
-// the same value).
+// rates launch (one wave; every workgroup folds them in the same order).  The
+// sums are exact: an influence sum is at most the edge count, below 2^31.
 __device__ double markov_tau(const MkArgs& a, uint32_t lane)
 {
-    unsigned long long A = 0, nE = 0, nI = 0;
-    uint32_t M = 0;
+    uint32_t A = 0, M = 0, nE = 0, nI = 0;
     for (uint32_t g = lane; g < a.G; g += 64) {
         const uint4 v = a.rpart[g];
         A += v.x;
@@ -94,12 +121,10 @@ __device__ double markov_tau(const MkArgs& a, uint32_t lane)
         nE += v.z;
         nI += v.w;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        A += __shfl_xor(A, off, 64);
-        M = max(M, (uint32_t)__shfl_xor((int)M, off, 64));
-        nE += __shfl_xor(nE, off, 64);
-        nI += __shfl_xor(nI, off, 64);
-    }
+    A = wave_fold<false>(A);
+    M = wave_fold<true>(M);
+    nE = wave_fold<false>(nE);
+    nI = wave_fold<false>(nI);
     const double L = (double)a.beta * (double)A + (double)a.sigma * (double)nE + (double)a.gamma * (double)nI;
     double mx = (double)a.beta * (double)M;
     if (nE > 0) mx = fmax(mx, (double)a.sigma);
@@ -110,212 +135,281 @@ __device__ double markov_tau(const MkArgs& a, uint32_t lane)
     return tau;
 }
 
-__global__ __launch_bounds__(MTPB) void mk_draw_kernel(MkArgs a)
+// The four states of a lane's nodes i .. i + 3 (state is padded past n), the
+// ones past `end` as 7, which is no compartment.
+__device__ __forceinline__ uint32_t load_states(const uint8_t* state, uint32_t i, uint32_t end)
 {
-    constexpr int NW = MTPB / 64;
+    uint32_t w = 0x07070707u;
+    if (i < end) {
+        w = *(const uint32_t*)(state + i);
+        const uint32_t nv = end - i;
+        if (nv < NPL) w |= 0x07070707u << (8u * nv);
+    }
+    return w;
+}
+
+__global__ __launch_bounds__(MTPB) void mk_step_kernel(MkArgs a)
+{
+    constexpr uint32_t NW = MTPB / 64;
+    __shared__ uint32_t s_lam[NW][64 * NPL]; // queued draws of each wave: the rate,
+    __shared__ uint32_t s_who[NW][64 * NPL]; // the node in the tile | state << 16,
+    __shared__ uint32_t s_key[NW][64 * NPL]; // and the caller's node id
+    __shared__ uint32_t s_event[MTPB * NPL]; // node | EV_LEAVE when it stopped being infectious
     __shared__ uint32_t s_ev, s_fired;
-    __shared__ uint32_t s_cnt[NW][4];
     __shared__ double s_tau;
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t tpb = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long k = a.ctl->step + a.step_off;
-    // one wave per workgroup folds the rate partials
-    if (wave == 0) {
-        const double t = markov_tau(a, lane);
-        if (lane == 0) {
-            s_tau = t;
+    const uint32_t base = blockIdx.x * a.span;
+    const uint32_t end = min(a.n, base + a.span);
+    uint32_t events = 0, fired = 0; // of the whole workgroup (thread 0's hold)
+    bool pushing = a.inertial_max != 0u;
+    float tf = 0.0f;
+    for (uint32_t tile = base; tile < end; tile += tpb * NPL) {
+        const uint32_t i = tile + tid * NPL;
+        const uint32_t w = load_states(a.state, i, end);
+        int4 f = make_int4(0, 0, 0, 0);
+        if (i < end) f = *(const int4*)(a.infl + i);
+        if (tile == base && wave == 0) {
+            const double t = markov_tau(a, lane);
+            if (lane == 0) {
+                s_tau = t;
+                if (blockIdx.x == 0) {
+                    a.tau_hist[k % a.H] = (float)t;
+                    *a.elapsed += t;
+                }
+            }
+        }
+        if (tid == 0) {
             s_ev = 0;
             s_fired = 0;
         }
-    }
-    __syncthreads();
-    const double tau = s_tau;
-    const float tf = (float)tau;
-    const uint32_t base = blockIdx.x * a.span;
-    const uint32_t end = min(a.n, base + a.span);
-    uint32_t c[4] = {0, 0, 0, 0};
-    uint32_t nfire = 0;
-    for (uint32_t i0 = base + wave * 64; i0 < end; i0 += MTPB) {
-        const uint32_t i = i0 + lane;
-        const bool valid = i < end;
-        const int x = valid ? (int)a.state[i] : ST_R;
-        const int f = x == ST_S ? a.infl[i] : 0;
-        const float lam = x == ST_S ? a.beta * (float)f : x == ST_E ? a.sigma : x == ST_I ? a.gamma : 0.0f;
-        bool fire = false;
-        if (lam > 0.0f) {
-            const uint4 w = fsd::philox4x32_10(make_uint4((uint32_t)a.orig_id[i], (uint32_t)k, 0u, 0u), a.key0, a.key1);
-            const float u = (float)(w.x >> 8) * 0x1p-24f;
-            fire = u < -expm1f(-lam * tf);
-        }
-        const int xn = fire ? next_state(a.model, x) : x;
-        if (fire) a.state[i] = (uint8_t)xn;
-        nfire += (uint32_t)__popcll(__ballot(fire));
-        // a change of infectiousness is an event of this workgroup's region
-        const bool ev = fire && ((xn == ST_I) != (x == ST_I));
-        const unsigned long long m = __ballot(ev);
-        if (m) {
-            uint32_t pos = 0;
-            if (lane == 0) pos = atomicAdd(&s_ev, (uint32_t)__popcll(m)); // LDS
-            pos = __shfl(pos, 0, 64);
-            if (ev) a.events[base + pos + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = i | (x == ST_I ? EV_LEAVE : 0u);
+        __syncthreads();
+        tf = (float)s_tau;
+        // the nodes with a positive rate, packed
+        uint32_t qn = 0;
+        const int fl[NPL] = {f.x, f.y, f.z, f.w};
+        uint32_t key[NPL];
+        float lam[NPL];
+#pragma unroll
+        for (uint32_t j = 0; j < NPL; ++j) {
+            const uint32_t x = (w >> (8u * j)) & 7u;
+            lam[j] = x == (uint32_t)ST_S ? a.beta * (float)fl[j] : x == (uint32_t)ST_E ? a.sigma : x == (uint32_t)ST_I ? a.gamma : 0.0f;
+            key[j] = lam[j] > 0.0f ? (uint32_t)a.orig_id[i + j] : 0u;
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) c[q] += (uint32_t)__popcll(__ballot(valid && xn == q));
-    }
-    if (lane == 0) {
-        for (int q = 0; q < 4; ++q) s_cnt[wave][q] = c[q];
-        atomicAdd(&s_fired, nfire); // LDS
-    }
-    __syncthreads();
-    if (tid < 4) {
-        uint32_t t = 0;
-        for (int w = 0; w < NW; ++w) t += s_cnt[w][tid];
-        a.part[((size_t)a.step_off * a.G + blockIdx.x) * 4 + tid] = t;
-    }
-    if (tid == 0) {
-        a.ev_cnt[blockIdx.x] = s_ev;
-        a.fired[blockIdx.x] = s_fired;
-        if (blockIdx.x == 0) {
-            a.tau_hist[k % a.H] = tf;
-            *a.elapsed += tau;
+        for (uint32_t j = 0; j < NPL; ++j) {
+            const bool need = lam[j] > 0.0f;
+            const unsigned long long m = __ballot(need);
+            if (need) {
+                const uint32_t at = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                s_lam[wave][at] = __float_as_uint(lam[j]);
+                s_who[wave][at] = (tid * NPL + j) | (((w >> (8u * j)) & 7u) << 16);
+                s_key[wave][at] = key[j];
+            }
+            qn += (uint32_t)__popcll(m);
         }
-    }
-}
-
-// Inertial Mode.  The events of all regions, taken in region order, are
-// spread over every lane of the grid: each workgroup builds the exclusive
-// prefix of the region counts in LDS and each lane finds the region of its
-// event by binary search, then pushes +-1 to the event's out-neighbours
-// (non-returning integer atomics).
-constexpr uint32_t MAX_REGIONS = 1024;
-
-__global__ __launch_bounds__(PTPB) void mk_push_kernel(MkArgs a)
-{
-    __shared__ uint32_t s_pre[MAX_REGIONS + 1];
-    __shared__ uint32_t s_fire[PTPB / 64];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const unsigned long long k = a.ctl->step + a.step_off;
-    // region counts into LDS (all threads), transitions summed per wave
-    uint32_t f = 0;
-    for (uint32_t g = tid; g < a.G; g += PTPB) {
-        s_pre[g] = a.ev_cnt[g];
-        f += a.fired[g];
-    }
-    for (int off = 32; off > 0; off >>= 1) f += __shfl_xor(f, off, 64);
-    if (lane == 0) s_fire[wave] = f;
-    __syncthreads();
-    // exclusive prefix of the counts by wave 0: lane l scans its block of
-    // ceil(G / 64) regions, then the block sums are scanned across lanes
-    if (wave == 0) {
-        const uint32_t per = (a.G + 63) / 64;
-        const uint32_t g0 = lane * per, g1 = min(a.G, g0 + per);
-        uint32_t sum = 0;
-        for (uint32_t g = g0; g < g1; ++g) sum += s_pre[g];
-        uint32_t inc = sum;
-        for (uint32_t off = 1; off < 64; off <<= 1) {
-            const uint32_t v = __shfl_up(inc, off, 64);
-            if (lane >= off) inc += v;
-        }
-        uint32_t run = inc - sum;
-        for (uint32_t g = g0; g < g1; ++g) {
-            const uint32_t c = s_pre[g];
-            s_pre[g] = run;
-            run += c;
-        }
-        if (lane == 63) s_pre[a.G] = inc;
-    }
-    __syncthreads();
-    if (blockIdx.x == 0 && tid == 0) {
-        a.ev_hist[k % a.H] = s_pre[a.G];
-        uint32_t t = 0;
-        for (int w = 0; w < PTPB / 64; ++w) t += s_fire[w];
-        a.fired[a.G] = t;
-    }
-    const uint32_t total = s_pre[a.G];
-    if (total > a.inertial_max) return;
-    const int32_t* __restrict__ out_ind = a.out_ind;
-    const uint8_t* __restrict__ state = a.state;
-    for (uint32_t j = blockIdx.x * PTPB + tid; j < total; j += gridDim.x * PTPB) {
-        uint32_t lo = 0, hi = a.G; // s_pre[lo] <= j < s_pre[hi]
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (s_pre[mid] <= j) lo = mid;
-            else hi = mid;
-        }
-        const uint32_t e = a.events[(size_t)lo * a.span + (j - s_pre[lo])];
-        const uint32_t node = e & ~EV_LEAVE;
-        const int d = (e & EV_LEAVE) ? -1 : 1;
-        // without I -> S, a node that is not susceptible never reads its
-        // influence again: only susceptible targets are updated.  Targets go
-        // eight at a time: their ids, then their states, then the atomics,
-        // so a lane waits for two loads per eight targets, not per target.
-        const bool all = a.model == FS_MARKOV_SIS;
-        const int32_t t1 = a.out_ptr[node + 1];
-        for (int32_t t = a.out_ptr[node]; t < t1; t += 8) {
-            int32_t tg[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) tg[q] = t + q < t1 ? out_ind[t + q] : -1;
-            bool go[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) go[q] = tg[q] >= 0 && (all || state[tg[q]] == ST_S);
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (go[q]) atomicAdd(&a.infl[tg[q]], d);
-        }
-    }
-}
-
-// Control Mode recount (when the step's events were many, or after a state
-// change) and the rate partials of the current state.
-__global__ __launch_bounds__(MTPB) void mk_rates_kernel(MkArgs a)
-{
-    constexpr int NW = MTPB / 64;
-    __shared__ uint4 s_p[NW];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const unsigned long long k = a.ctl->step + a.step_off;
-    const uint32_t events = a.ev_hist[k % a.H];
-    // a step without transitions changed nothing: the partials still hold
-    if (!a.force_control && a.fired[a.G] == 0) return;
-    const bool control = a.force_control || events > a.inertial_max;
-    const uint32_t base = blockIdx.x * a.span;
-    const uint32_t end = min(a.n, base + a.span);
-    uint32_t A = 0, M = 0, nE = 0, nI = 0;
-    for (uint32_t i0 = base + wave * 64; i0 < end; i0 += MTPB) {
-        const uint32_t i = i0 + lane;
-        const bool valid = i < end;
-        const int x = valid ? (int)a.state[i] : ST_R;
-        int f = 0;
-        if (valid) {
-            if (control) {
-                for (int32_t e = a.row_ptr[i]; e < a.row_ptr[i + 1]; ++e) f += a.state[a.col_ind[e]] == ST_I;
-                a.infl[i] = f;
-            } else if (x == ST_S) {
-                f = a.infl[i];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        uint32_t nfire = 0;
+        for (uint32_t q0 = 0; q0 < qn; q0 += 64) {
+            bool fire = false, ev = false;
+            uint32_t node = 0;
+            int x = ST_R;
+            if (q0 + lane < qn) {
+                const uint32_t who = s_who[wave][q0 + lane];
+                node = tile + (who & 0xFFFFu);
+                x = (int)(who >> 16);
+                const uint4 r = fsd::philox4x32_10(make_uint4(s_key[wave][q0 + lane], (uint32_t)k, 0u, 0u), a.key0, a.key1);
+                fire = fsd::bernoulli((float)(r.x >> 8) * 0x1p-24f, __uint_as_float(s_lam[wave][q0 + lane]) * tf);
+                if (fire) {
+                    const int xn = next_state(a.model, x);
+                    a.state[node] = (uint8_t)xn;
+                    ev = (xn == ST_I) != (x == ST_I);
+                }
+            }
+            nfire += (uint32_t)__popcll(__ballot(fire));
+            const unsigned long long m = __ballot(ev);
+            if (m) {
+                uint32_t pos = 0;
+                if (lane == 0) pos = atomicAdd(&s_ev, (uint32_t)__popcll(m)); // LDS
+                pos = __builtin_amdgcn_readfirstlane(pos);
+                if (ev) s_event[pos + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = node | (x == ST_I ? EV_LEAVE : 0u);
             }
         }
-        if (x == ST_S) {
-            A += (uint32_t)f;
-            M = max(M, (uint32_t)f);
+        if (lane == 0 && nfire) atomicAdd(&s_fired, nfire); // LDS
+        __syncthreads();
+        const uint32_t nev = s_ev;
+        events += nev;
+        fired += s_fired;
+        // (a step of many events is recounted anyway: past its share of them
+        // a workgroup leaves the pushes to the recount)
+        if (events > a.wg_max) pushing = false;
+        if (pushing) {
+            // eight lanes per event take eight targets each at a time (their
+            // ids, then their states, then the atomics); lists of more than 64
+            // targets (hubs) are left to whole waves
+            const bool all = a.model == FS_MARKOV_SIS;
+            const int32_t* __restrict__ out_ind = a.out_ind;
+            const uint8_t* state = a.state;
+            auto push = [&](uint32_t t0, uint32_t t1, uint32_t at, uint32_t stride, int d) {
+                for (uint32_t t = t0 + at; t < t1; t += 8 * stride) {
+                    int32_t tg[8];
+                    bool go[8];
+#pragma unroll
+                    for (uint32_t u = 0; u < 8; ++u) tg[u] = t + u * stride < t1 ? out_ind[t + u * stride] : -1;
+#pragma unroll
+                    for (uint32_t u = 0; u < 8; ++u) go[u] = tg[u] >= 0 && (all || state[tg[u]] == ST_S);
+#pragma unroll
+                    for (uint32_t u = 0; u < 8; ++u)
+                        if (go[u]) atomicAdd(&a.pending[tg[u]], d);
+                }
+            };
+            const uint32_t sub = lane & 7u;
+            for (uint32_t e0 = wave * 8; e0 < nev; e0 += tpb / 8) {
+                const uint32_t e = e0 + (lane >> 3);
+                const uint32_t v = e < nev ? s_event[e] : 0u;
+                const uint32_t node = v & ~EV_LEAVE;
+                const uint32_t t0 = e < nev ? (uint32_t)a.out_ptr[node] : 0u;
+                const uint32_t t1 = e < nev ? (uint32_t)a.out_ptr[node + 1] : 0u;
+                const bool lng = t1 - t0 > 64u;
+                if (!lng) push(t0, t1, sub, 8u, (v & EV_LEAVE) ? -1 : 1);
+                for (unsigned long long lm = __ballot(lng && sub == 0u); lm != 0ull; lm &= lm - 1ull) {
+                    const int l = __builtin_ctzll(lm);
+                    const uint32_t u0 = (uint32_t)__shfl((int)t0, l, 64), u1 = (uint32_t)__shfl((int)t1, l, 64);
+                    const uint32_t lv = (uint32_t)__shfl((int)v, l, 64);
+                    push(u0, u1, lane, 64u, (lv & EV_LEAVE) ? -1 : 1);
+                }
+            }
         }
-        nE += x == ST_E;
-        nI += x == ST_I;
+        if (tile + tpb * NPL < end) __syncthreads(); // (the event list is reused)
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        A += __shfl_xor(A, off, 64);
-        M = max(M, (uint32_t)__shfl_xor((int)M, off, 64));
-        nE += __shfl_xor(nE, off, 64);
-        nI += __shfl_xor(nI, off, 64);
+    if (tid == 0) {
+        a.ev_cnt[blockIdx.x] = events;
+        a.fired[blockIdx.x] = fired | (pushing ? 0u : SKIPPED);
     }
-    if (lane == 0) s_p[wave] = make_uint4(A, M, nE, nI);
+}
+
+// The influences after a step (its pending changes, or in Control Mode and
+// after a state change a recount), and the partials and counts of the new
+// states.
+__global__ __launch_bounds__(MTPB) void mk_rates_kernel(MkArgs a)
+{
+    constexpr uint32_t NW = MTPB / 64;
+    __shared__ uint4 s_p[NW], s_c[NW];
+    __shared__ uint32_t s_t[NW][2];
+    const uint32_t tpb = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = tpb >> 6;
+    const unsigned long long k = a.ctl->step + a.step_off;
+    const uint32_t base = blockIdx.x * a.span;
+    const uint32_t end = min(a.n, base + a.span);
+    // the first tile's arrays and the step's totals, together
+    uint32_t i = base + tid * NPL;
+    uint32_t w = load_states(a.state, i, end);
+    int4 f = make_int4(0, 0, 0, 0), d = make_int4(0, 0, 0, 0);
+    if (i < end) {
+        f = *(const int4*)(a.infl + i);
+        d = *(const int4*)(a.pending + i);
+    }
+    uint32_t ev = 0, fi = 0, skip = 0;
+    for (uint32_t g = tid; g < a.G; g += tpb) {
+        ev += a.ev_cnt[g];
+        const uint32_t v = a.fired[g];
+        fi += v & ~SKIPPED;
+        skip |= v & SKIPPED;
+    }
+    ev = wave_fold<false>(ev);
+    fi = wave_fold<false>(fi);
+    if (__ballot(skip != 0u) != 0ull) fi |= SKIPPED;
+    if (lane == 0) {
+        s_t[wave][0] = ev;
+        s_t[wave][1] = fi;
+    }
+    __syncthreads();
+    ev = fi = skip = 0;
+    for (uint32_t v = 0; v < nw; ++v) {
+        ev += s_t[v][0];
+        fi += s_t[v][1] & ~SKIPPED;
+        skip |= s_t[v][1] & SKIPPED;
+    }
+    uint4* part = (uint4*)a.part + (size_t)a.step_off * a.G + blockIdx.x;
+    if (!a.force_control) {
+        if (blockIdx.x == 0 && tid == 0) a.ev_hist[k % a.H] = ev;
+        // a step without transitions changed nothing: the partials still hold
+        if (fi == 0) {
+            if (tid == 0) *part = a.wcnt[blockIdx.x];
+            return;
+        }
+    }
+    const bool control = a.force_control || ev > a.inertial_max || skip != 0u;
+    uint32_t A = 0, M = 0, nE = 0, nI = 0, nS = 0;
+    if (control) {
+        for (uint32_t v = base + tid; v < end; v += tpb) {
+            const int x = (int)a.state[v];
+            int c = 0;
+            for (int32_t e = a.row_ptr[v]; e < a.row_ptr[v + 1]; ++e) c += a.state[a.col_ind[e]] == ST_I;
+            a.infl[v] = c;
+            a.pending[v] = 0;
+            if (x == ST_S) {
+                A += (uint32_t)c;
+                M = max(M, (uint32_t)c);
+            }
+            nS += x == ST_S;
+            nE += x == ST_E;
+            nI += x == ST_I;
+        }
+    } else {
+        for (uint32_t tile = base; tile < end; tile += tpb * NPL) {
+            if (tile != base) {
+                i = tile + tid * NPL;
+                w = load_states(a.state, i, end);
+                f = d = make_int4(0, 0, 0, 0);
+                if (i < end) {
+                    f = *(const int4*)(a.infl + i);
+                    d = *(const int4*)(a.pending + i);
+                }
+            }
+            if ((d.x | d.y | d.z | d.w) != 0) {
+                f = make_int4(f.x + d.x, f.y + d.y, f.z + d.z, f.w + d.w);
+                *(int4*)(a.infl + i) = f;
+                *(int4*)(a.pending + i) = make_int4(0, 0, 0, 0);
+            }
+            const int fl[NPL] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+            for (uint32_t j = 0; j < NPL; ++j) {
+                const uint32_t v = (w >> (8u * j)) & 7u ? 0u : (uint32_t)fl[j]; // S nodes only
+                A += v;
+                M = max(M, v);
+            }
+            const uint32_t b0 = w & 0x01010101u, b1 = (w >> 1) & 0x01010101u;
+            nS += (uint32_t)__popc(~(b0 | b1) & 0x01010101u);
+            nE += (uint32_t)__popc(b0 & ~b1);
+            nI += (uint32_t)__popc(b1 & ~b0);
+        }
+    }
+    A = wave_fold<false>(A);
+    M = wave_fold<true>(M);
+    nE = wave_fold<false>(nE);
+    nI = wave_fold<false>(nI);
+    nS = wave_fold<false>(nS);
+    if (lane == 0) {
+        s_p[wave] = make_uint4(A, M, nE, nI);
+        s_c[wave].x = nS;
+    }
     __syncthreads();
     if (tid == 0) {
         uint4 t = make_uint4(0, 0, 0, 0);
-        for (int w = 0; w < NW; ++w) {
-            t.x += s_p[w].x;
-            t.y = max(t.y, s_p[w].y);
-            t.z += s_p[w].z;
-            t.w += s_p[w].w;
+        uint32_t S = 0;
+        for (uint32_t v = 0; v < nw; ++v) {
+            t.x += s_p[v].x;
+            t.y = max(t.y, s_p[v].y);
+            t.z += s_p[v].z;
+            t.w += s_p[v].w;
+            S += s_c[v].x;
         }
         a.rpart[blockIdx.x] = t;
+        const uint4 c = make_uint4(S, t.z, t.w, end - base - S - t.z - t.w);
+        a.wcnt[blockIdx.x] = c;
+        if (!a.force_control) *part = c;
     }
 }
 
@@ -361,7 +455,9 @@ struct fs_markov {
     bool own_stream = false;
     uint8_t* d_state = nullptr;
     int32_t* d_infl = nullptr;
-    uint32_t* d_events = nullptr;
+    int32_t* d_pending = nullptr;
+    uint4* d_wcnt = nullptr;
+    uint32_t tpb = 1024; // threads per workgroup
     uint32_t* d_ev_cnt = nullptr;
     uint32_t* d_fired = nullptr;
     uint4* d_rpart = nullptr;
@@ -418,7 +514,7 @@ void release_markov(fs_markov* m)
     if (m->stream) (void)hipStreamSynchronize(m->stream); // (blocks may return to a caller's allocator)
     if (m->exec) (void)hipGraphExecDestroy(m->exec);
     if (m->graph) (void)hipGraphDestroy(m->graph);
-    for (void* p : {(void*)m->d_state, (void*)m->d_infl, (void*)m->d_events, (void*)m->d_ev_cnt, (void*)m->d_fired,
+    for (void* p : {(void*)m->d_state, (void*)m->d_infl, (void*)m->d_pending, (void*)m->d_wcnt, (void*)m->d_ev_cnt, (void*)m->d_fired,
                     (void*)m->d_rpart,
                     (void*)m->d_part, (void*)m->d_hist, (void*)m->d_tau, (void*)m->d_evh, (void*)m->d_elapsed,
                     (void*)m->d_ctl})
@@ -436,7 +532,7 @@ hipError_t refresh(fs_markov* m)
     a.force_control = 1;
     a.step_off = 0;
     void* argv[] = {&a};
-    return hipLaunchKernel((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(fsm::MTPB), argv, 0, m->stream);
+    return hipLaunchKernel((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(m->tpb), argv, 0, m->stream);
 }
 
 struct MkSeq {
@@ -460,8 +556,6 @@ void make_seq(fs_markov* m, uint32_t r, MkSeq& q)
     q.hist = m->d_hist;
 }
 
-uint32_t push_grid(const fs_markov* m) { return std::max(1u, std::min((m->G + 3) / 4, 1024u)); }
-
 fs_status build_exec(fs_markov* m, uint32_t b)
 {
     MkSeq q;
@@ -482,9 +576,8 @@ fs_status build_exec(fs_markov* m, uint32_t b)
     fs_status st;
     for (uint32_t j = 0; j < b; ++j) {
         void* argv[] = {&q.step[j]};
-        if ((st = add((const void*)&fsm::mk_draw_kernel, dim3(m->G), dim3(fsm::MTPB), argv)) != FS_OK) return st;
-        if ((st = add((const void*)&fsm::mk_push_kernel, dim3(push_grid(m)), dim3(fsm::PTPB), argv)) != FS_OK) return st;
-        if ((st = add((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(fsm::MTPB), argv)) != FS_OK) return st;
+        if ((st = add((const void*)&fsm::mk_step_kernel, dim3(m->G), dim3(m->tpb), argv)) != FS_OK) return st;
+        if ((st = add((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(m->tpb), argv)) != FS_OK) return st;
     }
     uint32_t* no_base = nullptr;
     void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H, &no_base};
@@ -499,10 +592,8 @@ fs_status launch_seq(fs_markov* m, uint32_t r)
     make_seq(m, r, q);
     for (uint32_t j = 0; j < r; ++j) {
         void* argv[] = {&q.step[j]};
-        FS_HIP(hipLaunchKernel((const void*)&fsm::mk_draw_kernel, dim3(m->G), dim3(fsm::MTPB), argv, 0, m->stream));
-        FS_HIP(hipLaunchKernel((const void*)&fsm::mk_push_kernel, dim3(push_grid(m)), dim3(fsm::PTPB), argv, 0,
-                               m->stream));
-        FS_HIP(hipLaunchKernel((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(fsm::MTPB), argv, 0, m->stream));
+        FS_HIP(hipLaunchKernel((const void*)&fsm::mk_step_kernel, dim3(m->G), dim3(m->tpb), argv, 0, m->stream));
+        FS_HIP(hipLaunchKernel((const void*)&fsm::mk_rates_kernel, dim3(m->G), dim3(m->tpb), argv, 0, m->stream));
     }
     uint32_t* no_base = nullptr;
     void* rargv[] = {&q.ctl, &q.part, &q.G, &q.C, &q.hist, &q.H, &no_base};
@@ -565,6 +656,9 @@ fs_status fs_markov_create(fs_graph* g, const fs_markov_params* p, fs_markov** o
                                                               ((int64_t)n + 63) / 64}));
     m->span = (((n + m->G - 1) / m->G) + 63) / 64 * 64;
     m->G = (n + m->span - 1) / m->span;
+    // four nodes per lane, in whole wavefronts (larger regions in tiles)
+    m->tpb = std::min(fsm::MTPB, (m->span / fsm::NPL + 63) / 64 * 64);
+    const size_t padded = ((size_t)n + 255) / 256 * 256;
     if (p->stream) {
         m->stream = (hipStream_t)p->stream;
     } else {
@@ -572,9 +666,10 @@ fs_status fs_markov_create(fs_graph* g, const fs_markov_params* p, fs_markov** o
         m->own_stream = true;
     }
     const size_t part_words = (size_t)m->chunk * m->G * 4;
-    if ((e = dev_alloc((void**)&m->d_state, n)) != hipSuccess ||
-        (e = dev_alloc((void**)&m->d_infl, (size_t)n * 4)) != hipSuccess ||
-        (e = dev_alloc((void**)&m->d_events, (size_t)m->G * m->span * 4)) != hipSuccess ||
+    if ((e = dev_alloc((void**)&m->d_state, padded)) != hipSuccess ||
+        (e = dev_alloc((void**)&m->d_infl, padded * 4)) != hipSuccess ||
+        (e = dev_alloc((void**)&m->d_pending, padded * 4)) != hipSuccess ||
+        (e = dev_alloc((void**)&m->d_wcnt, (size_t)m->G * sizeof(uint4))) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_ev_cnt, (size_t)m->G * 4)) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_fired, ((size_t)m->G + 1) * 4)) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_rpart, (size_t)m->G * sizeof(uint4))) != hipSuccess ||
@@ -585,8 +680,9 @@ fs_status fs_markov_create(fs_graph* g, const fs_markov_params* p, fs_markov** o
         (e = dev_alloc((void**)&m->d_elapsed, 8)) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_ctl, sizeof(fsi::Ctl))) != hipSuccess)
         return bad(e, "device allocation");
-    if ((e = hipMemsetAsync(m->d_state, 0, n, m->stream)) != hipSuccess ||
-        (e = hipMemsetAsync(m->d_infl, 0, (size_t)n * 4, m->stream)) != hipSuccess ||
+    if ((e = hipMemsetAsync(m->d_state, 0, padded, m->stream)) != hipSuccess ||
+        (e = hipMemsetAsync(m->d_infl, 0, padded * 4, m->stream)) != hipSuccess ||
+        (e = hipMemsetAsync(m->d_pending, 0, padded * 4, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_ev_cnt, 0, (size_t)m->G * 4, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_fired, 0, ((size_t)m->G + 1) * 4, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_hist, 0, (size_t)m->H * 16, m->stream)) != hipSuccess ||
@@ -603,7 +699,8 @@ fs_status fs_markov_create(fs_graph* g, const fs_markov_params* p, fs_markov** o
     a.out_ptr = g->d_out_ptr;
     a.out_ind = g->d_out_ind;
     a.orig_id = g->d_orig;
-    a.events = m->d_events;
+    a.pending = m->d_pending;
+    a.wcnt = m->d_wcnt;
     a.ev_cnt = m->d_ev_cnt;
     a.fired = m->d_fired;
     a.rpart = m->d_rpart;
@@ -631,6 +728,8 @@ fs_status fs_markov_create(fs_graph* g, const fs_markov_params* p, fs_markov** o
     a.inertial_max = p->inertial_max == -1 ? 0u
                    : p->inertial_max > 0   ? (uint32_t)std::min<int64_t>(p->inertial_max, 0xFFFFFFFFll)
                                            : (uint32_t)std::max(1.0, (double)g->nnz / 8.0 / dmean);
+    // (four times an even share: uneven regions still push)
+    a.wg_max = (uint32_t)std::min<uint64_t>(0xFFFFFFFFull, 4ull * a.inertial_max / m->G + 64ull);
     if ((e = refresh(m)) != hipSuccess || (e = hipStreamSynchronize(m->stream)) != hipSuccess)
         return bad(e, "initialisation");
     *out = m;

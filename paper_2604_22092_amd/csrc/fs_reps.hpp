@@ -95,24 +95,6 @@ __device__ __forceinline__ uint32_t block_bits(rsrc_t gbits, uint32_t col, int32
     return __builtin_amdgcn_ubfe(v, b & 7u, 1u << LGW);
 }
 
-// Whether u < 1 - exp(-y) for the comparison the step makes in FP32
-// (u < -expm1f(-y)).  The Taylor bounds y - y^2/2 + y^3/6 - y^4/24 <= 1 -
-// exp(-y) <= y - y^2/2 + y^3/6, widened by 1e-6 y (many times the rounding of
-// expm1f and of the bounds for y <= 1), decide all but about y^4/24 of the
-// draws; only a wavefront holding one of those evaluates expm1f.
-__device__ __forceinline__ bool bernoulli(float u, float y)
-{
-    const float up = y * __builtin_fmaf(-y, __builtin_fmaf(y, -1.0f / 6.0f, 0.5f), 1.0f);
-    const float m = 1e-6f * y;
-    const float y2 = y * y;
-    const bool yes = u < up - __builtin_fmaf(y2 * y2, 1.0f / 24.0f, m);
-    const bool no = u >= up + m;
-    const bool sure = y <= 1.0f && (yes || no);
-    bool fire = yes;
-    if (!sure) fire = u < -expm1f(-y);
-    return fire;
-}
-
 template <int STORAGE, int LGW>
 __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S, uint32_t block, uint32_t nblocks)
 {
@@ -334,7 +316,7 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
                          ks = __builtin_amdgcn_readfirstlane(kk);
                 asm volatile("" : "+s"(k0), "+s"(k1), "+s"(ks));
                 const uint32_t w = fsd::philox4x32_10(make_uint4(nid, ks, l & (R - 1u), 0u), k0, k1).x >> 8;
-                fire = bernoulli((float)w * 0x1p-24f, lam * dt);
+                fire = fsd::bernoulli((float)w * 0x1p-24f, lam * dt);
             }
             const unsigned long long fm = __ballot(fire);
             if (fm == 0ull) return;
