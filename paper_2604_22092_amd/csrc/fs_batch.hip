@@ -156,7 +156,7 @@ fs_status rebuild_tables(fs_batch* b)
         r.G = s->G;
         r.C = 4u * (uint32_t)s->R;
         r.H = (uint32_t)s->H;
-        r.base = s->lgW >= 0 ? s->d_base : nullptr;
+        r.base = s->d_base;
         red.push_back(r);
         b->chunk = std::min(b->chunk, s->chunk);
     }

@@ -15,6 +15,8 @@ constexpr int WG = 256;
 // streaming variant with many replicas leaves up to max_step_grid(R) * 4R
 // partial counts, one block reads them all).
 constexpr int RED_TPB = 1024;
+// Words of step totals its last block holds at a time.
+constexpr int RED_TILE = 4096;
 // Step kernel variants, all walking 64-unit chunks per wavefront:
 //  MODE_STREAM   bitmap read through the caches; STREAM_TPB threads per workgroup;
 //  MODE_RESIDENT the whole bitmap (up to RESIDENT_BITS units) held in LDS;
@@ -119,7 +121,7 @@ struct StepArgs {
     void* iota1;          // iota[k & 1] and writes iota[(k + 1) & 1]
     float* rates;         // optional per-unit lambda (debug), [n][R]; nullptr: none
     const Ctl* ctl;
-    uint32_t* part;       // per-workgroup counts [chunk slot][grid][R][4]
+    uint32_t* part;       // per-workgroup transitions [chunk slot][grid][R][4]
     int32_t n;
     int32_t lgR;          // R = 1 << lgR replicas
     uint32_t step_off;    // j: this launch runs step ctl->step + j, partial slot j
@@ -197,8 +199,7 @@ struct StepArgs {
     const ShedDev* shed_dev; // the profile s, in device memory (LawsDev::shed)
     // active-chunk compaction (nullptr act: off): the launch walks the chunks
     // act[2 .. 2 + act[0]) (ascending); every other chunk holds only R units
-    // and is skipped, and act[1] R units per replica are added to the counts
-    // of workgroup 0.  When live is set (the last step of a launch sequence,
+    // and is skipped.  When live is set (the last step of a launch sequence,
     // whose flags the next sequence's refresh reads), every processed chunk
     // stores 1 in live[chunk] when it held a unit that is not R at the start
     // of the step, else 0.
@@ -266,7 +267,7 @@ struct RedArgs {
     uint32_t* part;
     uint32_t* hist;
     uint32_t G, C, H, pad;
-    uint32_t* base; // replica step: the counts before the sequence (see reduce_body), else nullptr
+    uint32_t* base; // the counts before the sequence (see reduce_body)
 };
 
 // Upper bound on step workgroups (they loop over tiles beyond it), chosen so

@@ -24,25 +24,30 @@ namespace fsk {
 // Sums per-workgroup count partials.  Block j handles slot j: rows of C
 // counters from G workgroups, part[j][g][c]; the totals go to
 // out[((base + j) mod H)][c] where base = ctl->step (0 without ctl).
-// Requires C <= RED_TPB and RED_TPB % C == 0 (C = 4R with R a power of two
-// <= 64).  Each thread keeps eight independent sums of the rows it reads (so
+// Requires C a power of two <= RED_TPB (C = 4R with R a power of two <= 64).  Each thread keeps eight independent sums of the rows it reads (so
 // eight loads are in flight), and the block's sums are folded by a tree in
 // LDS (integer sums: the order does not change them).
 // With a ctl, the r blocks of the launch end the launch sequence: each takes
 // a ticket in ctl->done once its reads of ctl->step are done, and the last
 // one adds r to ctl->step and clears the count (so the sequence needs no
 // launch of its own for the advance).
-// With a base, the partials are the replica step's transitions, [replica][S ->
-// E, E -> I, I -> R, unused]: block j leaves its totals in the first row of
+// With a base, the partials are the step's transitions, [replica][S -> E, E ->
+// I, I -> R, unused]: block j leaves its totals in the first row of
 // slot j, and the last block walks the slots, turning base, the counts before
-// the sequence, into the counts after each step (r additions per counter:
-// 0.1 us per step, against a scan of every unit's state in the step).
+// the sequence, into the counts after each step (r additions per counter,
+// against a tally of every unit's state in every step).
 __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G, uint32_t C, uint32_t* out,
                                             uint32_t H, uint32_t j, uint32_t r, uint32_t* base)
 {
     __shared__ uint32_t s[RED_TPB];
+    __shared__ uint32_t s_tile[RED_TILE];
     __shared__ uint32_t s_last;
     const uint32_t t = threadIdx.x;
+    const uint32_t lgC = (uint32_t)__builtin_ctz(C);
+    const unsigned long long first = ctl ? ctl->step : 0ull;
+    // (every block reads what only the last one uses, before the ticket)
+    uint32_t n = base && t < C ? base[t] : 0u;
+    const uint32_t slot0 = (uint32_t)(first % H);
     // of a sequence longer than the ring only the last H steps are kept, so
     // no two blocks write one slot
     if (base || (size_t)j + H >= (size_t)r) {
@@ -64,7 +69,6 @@ __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G
             __syncthreads();
         }
         if (t < C) {
-            const unsigned long long first = ctl ? ctl->step : 0ull;
             if (base)
                 __hip_atomic_store(&part[(size_t)j * G * C + t], s[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else
@@ -79,33 +83,39 @@ __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G
         }
         __syncthreads();
         if (!s_last) return;
-        if (base && t < C) {
-            // thread t carries counter t = (replica, compartment): it loses
-            // the transitions out of its compartment and gains those into it
-            const unsigned long long first = ctl->step;
-            const bool gain = (t & 3u) != 0u;
-            uint32_t n = base[t];
-            for (uint32_t i = 0; i < r; i += 8) {
-                uint32_t lost[8], got[8];
+        if (base) {
+            // the slots' totals by tiles of RED_TILE words (loaded together);
+            // thread t < C carries counter t = (replica, compartment): it
+            // loses the transitions out of its compartment and gains those
+            // into it
+            const uint32_t rows = RED_TILE >> lgC;
+            uint32_t slot = slot0; // the ring row of step i
+            for (uint32_t r0 = 0; r0 < r; r0 += rows) {
+                const uint32_t m = min(rows, r - r0);
 #pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) {
-                    const uint32_t* p = part + (size_t)min(i + u, r - 1u) * G * C;
-                    lost[u] = __hip_atomic_load(&p[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    got[u] = gain ? __hip_atomic_load(&p[t - 1u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                for (uint32_t u = 0; u < RED_TILE / RED_TPB; ++u) {
+                    const uint32_t i = u * RED_TPB + t;
+                    if (i < m << lgC)
+                        s_tile[i] = __hip_atomic_load(&part[((size_t)(r0 + (i >> lgC)) * G << lgC) + (i & (C - 1u))],
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) {
-                    if (i + u >= r) break;
-                    n += got[u] - lost[u];
-                    if ((size_t)(i + u) + H >= (size_t)r) out[(size_t)((first + i + u) % H) * C + t] = n;
+                __syncthreads();
+                if (t < C) {
+#pragma unroll 8
+                    for (uint32_t i = 0; i < m; ++i) {
+                        n += ((t & 3u) != 0u ? s_tile[i * C + t - 1u] : 0u) - s_tile[i * C + t];
+                        if ((size_t)(r0 + i) + H >= (size_t)r) out[(size_t)slot * C + t] = n;
+                        slot = slot + 1u == H ? 0u : slot + 1u;
+                    }
                 }
+                __syncthreads();
             }
-            base[t] = n;
+            if (t < C) base[t] = n;
         }
         __syncthreads();
         if (t == 0) {
             __hip_atomic_store(&ctl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctl->step, ctl->step + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&ctl->step, first + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -198,6 +208,36 @@ __global__ __launch_bounds__(WG) void recount_kernel(const void* state_v, int32_
         for (int w = 0; w < WG / 64; ++w) tot += s[w * 4 + threadIdx.x];
         part[blockIdx.x * 4 + threadIdx.x] = tot;
     }
+}
+
+// Exact counts of every replica added into base[R][4] (zeroed before): the
+// counts the steps' transitions are added to.
+template <int STORAGE>
+__global__ __launch_bounds__(WG) void count_all_kernel(const void* state_v, uint32_t total, int32_t lgR, uint32_t* base)
+{
+    using state_t = typename Store<STORAGE>::state_t;
+    const state_t* state = (const state_t*)state_v;
+    __shared__ uint32_t s[4 * 64];
+    const uint32_t C = 4u << lgR, rm = (1u << lgR) - 1u;
+    for (uint32_t i = threadIdx.x; i < C; i += WG) s[i] = 0;
+    __syncthreads();
+    if (lgR == 0) {
+        uint32_t c[4] = {0u, 0u, 0u, 0u};
+        for (uint32_t u0 = blockIdx.x * WG; u0 < total; u0 += gridDim.x * WG) {
+            const uint32_t u = u0 + threadIdx.x;
+            const int x = u < total ? (int)state[u] : -1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[q] += (uint32_t)__popcll(__ballot(x == q));
+        }
+        if ((threadIdx.x & 63u) == 0u)
+            for (int q = 0; q < 4; ++q) atomicAdd(&s[q], c[q]); // LDS
+    } else {
+        for (uint32_t u = blockIdx.x * WG + threadIdx.x; u < total; u += gridDim.x * WG)
+            atomicAdd(&s[(u & rm) * 4u + (uint32_t)state[u]], 1u); // LDS
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < C; i += WG)
+        if (s[i]) atomicAdd(&base[i], s[i]);
 }
 
 // Writes one replica's contiguous states and ages (caller's node order) into
@@ -334,19 +374,16 @@ __global__ __launch_bounds__(WG) void chunk_live_kernel(const void* state_v, uin
 }
 
 // Active-chunk list from the live flags (one workgroup of WG_REFRESH threads):
-// act[2 ..] = the chunks whose flag is set, ascending; act[0] = their number;
-// act[1] = the nodes of the other chunks (all their units are R, in every
-// replica).  Each thread takes 16 consecutive flags per tile; `live` is
-// padded with zeros to whole tiles.  rows = nodes per chunk.
+// act[2 ..] = the chunks whose flag is set, ascending; act[0] = their number
+// (act[1] is unused).  Each thread takes 16 consecutive flags per tile; `live`
+// is padded with zeros to whole tiles.
 __global__ __launch_bounds__(WG_REFRESH) void compact_refresh_kernel(const uint8_t* __restrict__ live,
-                                                                     uint32_t nchunks, uint32_t rows, uint32_t n,
-                                                                     uint32_t* __restrict__ act)
+                                                                     uint32_t nchunks, uint32_t* __restrict__ act)
 {
     constexpr uint32_t NWR = WG_REFRESH / 64;
     __shared__ uint32_t s_wave[NWR];
-    __shared__ uint32_t s_nodes[NWR];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t base = 0, nodes = 0;
+    uint32_t base = 0;
     for (uint32_t c0 = 0; c0 < nchunks; c0 += 16 * WG_REFRESH) {
         const uint32_t cf = c0 + 16 * tid;
         const uint4 w = *(const uint4*)(live + cf); // within the padded tile
@@ -374,23 +411,13 @@ __global__ __launch_bounds__(WG_REFRESH) void compact_refresh_kernel(const uint8
         uint32_t pos = base + before + inc - cnt;
         for (int i = 0; i < 16; ++i) {
             if ((mask >> i) & 1u) {
-                const uint32_t c = cf + (uint32_t)i;
-                act[2 + pos++] = c;
-                nodes += min(rows, n - c * rows);
+                act[2 + pos++] = cf + (uint32_t)i;
             }
         }
         base += tile;
         __syncthreads();
     }
-    for (int off = 32; off > 0; off >>= 1) nodes += __shfl_xor(nodes, off, 64);
-    if (lane == 0) s_nodes[wave] = nodes;
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t t = 0;
-        for (uint32_t v = 0; v < NWR; ++v) t += s_nodes[v];
-        act[0] = base;
-        act[1] = n - t;
-    }
+    if (tid == 0) act[0] = base;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -542,6 +569,18 @@ hipError_t launch_clear_u32(uint32_t* p, size_t n, hipStream_t s)
     unsigned g = grid_for(n, 256);
     if (g > 4096) g = 4096;
     hipLaunchKernelGGL(clear_u32_kernel, dim3(g), dim3(256), 0, s, p, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_count_all(int storage, const void* state, uint32_t total, int32_t lgR, uint32_t* base, hipStream_t s)
+{
+    hipError_t e = launch_clear_u32(base, (size_t)4 << lgR, s);
+    if (e != hipSuccess) return e;
+    const uint32_t g = std::max(1u, std::min((total + WG * 16u - 1u) / (WG * 16u), 1024u));
+    if (storage == 0)
+        hipLaunchKernelGGL(count_all_kernel<0>, dim3(g), dim3(WG), 0, s, state, total, lgR, base);
+    else
+        hipLaunchKernelGGL(count_all_kernel<1>, dim3(g), dim3(WG), 0, s, state, total, lgR, base);
     return hipGetLastError();
 }
 

@@ -53,7 +53,7 @@ hipError_t launch_hub_recount(const int32_t* row_ptr, const int32_t* col_ind, in
 // reduce_kernel(Ctl*, uint32_t* part, uint32_t G, uint32_t C, uint32_t* out, uint32_t H, uint32_t* base):
 // one block per slot, RED_TPB threads; with a ctl it also adds the slot count (its
 // grid) to the step index, which ends a launch sequence.  base (only with a
-// ctl): the partials are the replica step's transitions, added to base.
+// ctl): the partials are the step's transitions, added to base.
 const void* reduce_kernel_fn();
 // Segment partials of degree-binned rows (HeavyArgs): heavy_pressure_kernel
 // (WG threads, bits from global memory), or with resident set
@@ -110,7 +110,7 @@ hipError_t launch_rebuild_shed(int storage, const void* state, const void* age, 
 // Live flags of all nchunks chunks from the state.
 hipError_t launch_chunk_live(int storage, const void* state, uint32_t total, uint8_t* live, uint32_t nchunks,
                              hipStream_t s);
-// compact_refresh_kernel(const uint8_t* live, uint32_t nchunks, uint32_t rows, uint32_t n, uint32_t* act):
+// compact_refresh_kernel(const uint8_t* live, uint32_t nchunks, uint32_t* act):
 // one workgroup of WG_REFRESH threads; live padded with zeros to whole tiles of LIVE_TILE flags.
 const void* compact_refresh_kernel_fn();
 // clear_u32_kernel(uint32_t* p, size_t n): grid-stride zero fill, 256 threads.

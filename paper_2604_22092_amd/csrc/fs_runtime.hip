@@ -273,7 +273,7 @@ struct SeqArgs {
     uint32_t* base;
     // compaction refresh
     const uint8_t* live;
-    uint32_t nchunks, rows, n;
+    uint32_t nchunks;
     uint32_t* act;
     uint32_t* rates;
     size_t rates_words;
@@ -533,12 +533,19 @@ int replica_width(const fs_graph* g, const fs_sim_params& p, int lgR, int32_t li
 }
 
 // Threads and workgroups of a sim's step launch in a variant, or (lgW >= 0)
-// of the replica step.
+// of the replica step.  The LDS variants run one workgroup per compute unit, of
+// RESIDENT_TPB threads, or of as few as still give every chunk a wavefront of
+// its own: a small sim's launch is one pass, and four wavefronts that share a
+// SIMD take it in turn (regular d = 10, N = 1e4, 157 chunks: 10 workgroups of
+// 1024 threads 4.2 us per step, 157 of 64 threads 3.7; N = 1e5, 1563 chunks: 98 of
+// 1024 4.5, 196 of 512 4.1).
 void step_shape(const fs_sim* s, int mode, int lgW, uint32_t* tpb, uint32_t* G)
 {
     const size_t chunks = ((size_t)s->g->n * (size_t)s->R + 63) / 64;
     const bool stream = lgW >= 0 || mode == fsi::MODE_STREAM;
-    *tpb = stream ? fsi::STREAM_TPB : fsi::RESIDENT_TPB;
+    *tpb = fsi::STREAM_TPB;
+    if (!stream)
+        for (*tpb = 64; *tpb < (uint32_t)fsi::RESIDENT_TPB && (size_t)s->cus * (*tpb / 64) < chunks;) *tpb *= 2;
     const size_t waves = lgW >= 0 ? (chunks + ((size_t)1 << lgW) - 1) >> lgW : chunks;
     const size_t tiles = (waves + *tpb / 64 - 1) / (*tpb / 64); // workgroups with work
     *G = (uint32_t)std::min<size_t>(tiles, stream ? fsi::max_step_grid(s->R) : s->cus);
@@ -555,8 +562,6 @@ fs_status set_shape(fs_sim* s, int mode, int lgW)
         s->d_part = nullptr;
         FS_HIP(sim_alloc(s, (void**)&s->d_part, (size_t)s->chunk * G * (size_t)s->R * 4 * sizeof(uint32_t)));
     }
-    if (lgW >= 0 && !s->d_base) FS_HIP(sim_alloc(s, (void**)&s->d_base, (size_t)s->R * 4 * sizeof(uint32_t)));
-    if (lgW != s->lgW) s->base_stale = true;
     s->mode = mode;
     s->lgW = lgW;
     s->tpb = tpb;
@@ -567,7 +572,7 @@ fs_status set_shape(fs_sim* s, int mode, int lgW)
 
 hipError_t refresh_base(fs_sim* s)
 {
-    if (s->lgW < 0 || !s->base_stale) return hipSuccess;
+    if (!s->base_stale) return hipSuccess;
     const hipError_t e = fsk::launch_count_all(s->storage, s->d_state, (uint32_t)s->g->n << s->lgR, s->lgR, s->d_base,
                                                s->stream);
     if (e == hipSuccess) s->base_stale = false;
@@ -834,11 +839,9 @@ void make_seq(fs_sim* s, uint32_t r, SeqArgs& q)
     q.H = (uint32_t)s->H;
     q.r = r;
     q.hist = s->d_hist;
-    q.base = s->lgW >= 0 ? s->d_base : nullptr;
+    q.base = s->d_base;
     q.live = s->d_live;
     q.nchunks = s->nchunks;
-    q.rows = 64u >> s->lgR;
-    q.n = (uint32_t)s->g->n;
     q.act = s->d_act;
     q.rates = (uint32_t*)s->d_rates;
     q.rates_words = (size_t)s->g->n * (size_t)s->R;
@@ -870,7 +873,7 @@ fs_status build_graph_exec(fs_sim* s, int b)
             if ((st = add(fsk::clear_u32_kernel_fn(), dim3(clear_grid(q.rates_words)), dim3(256), cargv)) != FS_OK)
                 return st;
         }
-        void* fargv[] = {&q.live, &q.nchunks, &q.rows, &q.n, &q.act};
+        void* fargv[] = {&q.live, &q.nchunks, &q.act};
         if ((st = add(fsk::compact_refresh_kernel_fn(), dim3(1), dim3(fsi::WG_REFRESH), fargv)) != FS_OK) return st;
     }
     for (int j = 0; j < b; ++j) {
@@ -902,7 +905,7 @@ fs_status launch_sequence(fs_sim* s, uint32_t r)
             FS_HIP(hipLaunchKernel(fsk::clear_u32_kernel_fn(), dim3(clear_grid(q.rates_words)), dim3(256), cargv, 0,
                                    s->stream));
         }
-        void* fargv[] = {&q.live, &q.nchunks, &q.rows, &q.n, &q.act};
+        void* fargv[] = {&q.live, &q.nchunks, &q.act};
         FS_HIP(hipLaunchKernel(fsk::compact_refresh_kernel_fn(), dim3(1), dim3(fsi::WG_REFRESH), fargv, 0, s->stream));
     }
     for (uint32_t j = 0; j < r; ++j) {
@@ -1477,7 +1480,7 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
         (e = sim_alloc(s, (void**)&s->d_ctl, sizeof(fsi::Ctl))) != hipSuccess ||
         (e = sim_alloc(s, (void**)&s->d_hist, hist_words * sizeof(uint32_t))) != hipSuccess ||
         (e = sim_alloc(s, (void**)&s->d_part, part_words * sizeof(uint32_t))) != hipSuccess ||
-        (s->lgW >= 0 && (e = sim_alloc(s, (void**)&s->d_base, (size_t)R * 4 * sizeof(uint32_t))) != hipSuccess) ||
+        (e = sim_alloc(s, (void**)&s->d_base, (size_t)R * 4 * sizeof(uint32_t))) != hipSuccess ||
         (e = sim_alloc(s, (void**)&s->d_rc_part, RC_GRID * 4 * sizeof(uint32_t))) != hipSuccess ||
         (e = sim_alloc(s, (void**)&s->d_cnt4, 4 * sizeof(uint32_t))) != hipSuccess ||
         (s->mode == fsi::MODE_SUMMARY &&

@@ -122,10 +122,11 @@ struct fs_sim {
     uint32_t bit_words = 0;        // 64-bit words per infectivity bitmap
     uint32_t chunk = 0;            // steps per launch sequence (partial slots)
     // replica step (fs_reps.hpp): groups of 2^lgW chunks, or -1: the sim runs
-    // its variant's kernel.  d_base holds the counts [R][4] the step's
-    // transitions are added to; stale after a change of states from the host
-    // or steps of another kernel, and then recounted before the next sequence
+    // its variant's kernel
     int lgW = -1;
+    // the counts [R][4] the steps' transitions are added to; stale after a
+    // change of states from the host, and then recounted before the next
+    // launch sequence
     uint32_t* d_base = nullptr;
     bool base_stale = true;
     int64_t step = 0;      // index of the next step (host mirror of ctl->step)
@@ -209,8 +210,8 @@ uint32_t heavy_grid(const fs_sim* s);       // WG-thread heavy workgroups (batch
 uint32_t sim_heavy_grid(const fs_sim* s);   // the sim's own heavy launch
 uint32_t sim_heavy_block(const fs_sim* s);
 fsi::HeavyArgs heavy_args(const fs_sim* s);
-// The counts before the next launch sequence of a replica-step sim, if stale
-// (on the sim's stream; every path that queues its steps calls this first).
+// The counts before the sim's next launch sequence, if stale (on the sim's
+// stream; every path that queues its steps calls this first).
 hipError_t refresh_base(fs_sim* s);
 // Device bytes a sim of this graph and these parameters holds (an estimate
 // used for admission by memory budget).

@@ -172,12 +172,8 @@ constexpr int JB = 8;
 constexpr int JT = 16;
 // chunk_meta[c].y of a chunk whose rows do not share one light degree.
 constexpr uint32_t MIXED_CHUNK = 255u;
-// Chunks of 64 units each wavefront takes per pass; the hazards and draws of
-// a pass are evaluated on compacted lanes.
-#ifndef FS_CU
-#define FS_CU 1
-#endif
-constexpr int CU = FS_CU;
+// Chunks of 64 units each wavefront takes per pass (two measured slower).
+constexpr int CU = 1;
 // Issue the next pass's loads before processing the current one.
 #ifndef FS_PREFETCH
 #define FS_PREFETCH 1
@@ -284,7 +280,7 @@ template <class age_t>
 struct Pass {
     uint32_t chk[CU], base[CU], ud[CU], nvalid[CU];
     bool live[CU];
-    uint32_t xr[CU], agw[CU], dgr[CU], org[CU];
+    uint32_t xr[CU], agw[CU], dgr[CU];
     int32_t c[CU][UMAX];
     float tab[CU][3]; // hazard-table entry of the lane's age (issue_table)
     uint32_t ht[CU], hd[CU]; // pushed pressure of a binned unit: count of the last step, delta
@@ -307,7 +303,7 @@ __device__ __forceinline__ void pass_columns(const Pass<age_t>& P, int u, uint32
 // wavefront's queue of units that enter or leave I, whose pushes are made
 // after its walk (so no dependent load waits inside a pass, where it would
 // also wait for the next pass's prefetched loads).
-constexpr uint32_t PUSHQ = 128;
+constexpr uint32_t PUSHQ = 64;
 struct HubCtx {
     bool on;
     rsrc_t tr; // hub_T and hub_D, which follows it (2 * hub_units on)
@@ -519,9 +515,6 @@ __device__ __forceinline__ void issue_pass(const StepArgs& a, uint32_t first, ui
         // (uniform layouts have no heavy rows and arithmetic metadata: the
         // degree array is not needed)
         P.dgr[u] = UNIFORM ? 0u : BufIO<uint16_t>::ld(make_rsrc(a.ldeg + n0, nrows * 2u), q);
-        // graphs in a degree-sorted order (never uniform ones) key the draws
-        // by the caller's node id
-        P.org[u] = UNIFORM ? n0 + q : ld32(make_rsrc(a.orig_id + n0, nrows * 4u), q << 2);
         // binned rows with pushed pressure are the nodes from hub_base on:
         // their last count and this step's delta come with the pass
         if (!UNIFORM && H.on) {
@@ -858,211 +851,173 @@ __device__ __forceinline__ float pressure_heavy(const StepArgs& a, uint32_t node
     return (float)p;
 }
 
-// Evaluates f on the flagged items of CU chunks with the items packed into
-// consecutive lanes (64 per round), so a computation most lanes skip costs one
-// wavefront pass per 64 items instead of one per chunk.  xch is this
-// wavefront's 64-entry LDS exchange row; f maps a payload word to a result
-// word.  Only flagged items receive a result.
-template <int CU, class F>
-__device__ __forceinline__ void compact_apply(uint32_t* xch, uint32_t lane, const bool* flag,
-                                              const uint32_t* payload, uint32_t* result, F f)
+// Draws of a wavefront.  A pass queues its units with a positive rate; every
+// 64 of them, and what is left after the wavefront's last pass, are drawn
+// together, so the Philox rounds, the comparison, the transitions and the
+// hazards no table holds are evaluated once per 64 units that need them instead
+// of once per chunk (a chunk of 64 units holds a few).  Per step, drawn chunk by
+// chunk and queued: regular d = 10, N = 1e6 10.3 / 9.6 us; adaptive
+// Erdos-Renyi 8, N = 1e6 17.5 / 15.4; weighted Erdos-Renyi 10, N = 2e5, R = 4
+// 19.1 / 17.4; regular d = 8, N = 1e7 compact 79 / 73.  Wavefronts of a single
+// chunk only pay the way through LDS (regular d = 8, N = 6e4, R = 4: 4.6 / 5.0).
+// Pooling what a workgroup's wavefronts have left costs a barrier and a
+// search, more than the rounds it saves (N = 1e6 9.6 / 10.0).
+//  q[i].x: the rate, or the age of a unit whose hazard is yet to be evaluated;
+//  q[i].y: lane | pass << 6 | state << 29 | DRAW_EVAL, the pass's chunk being
+//          that of walk position wave + pass * waves.
+constexpr uint32_t DRAWQ = 128; // at most 63 left over plus one pass's 64
+constexpr uint32_t DRAW_EVAL = 0x80000000u;
+struct DrawCtx {
+    uint2* q;
+    uint32_t n;          // queued (wave-uniform)
+    uint32_t pass;       // passes begun
+    uint32_t wave, nwaves;
+};
+
+// Draws the last m (<= 64) queued units, one per lane: Bernoulli tau-leap, fire
+// when u < 1 - exp(-lambda dt), and the transitions of those that fire.  Their
+// pass stored the age of a unit that does not fire and the infectivity word of
+// the states before the step: a unit that fires overwrites its age (stores of
+// one wavefront to one address keep their order) and flips its bit (in the L2
+// that holds the word: no other compute unit touches it in this launch).
+template <int STORAGE, bool UNIFORM, bool SHED, bool EXTRA, bool HUBS>
+__device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32_t m, uint32_t lane, uint32_t k,
+                                           uint32_t* __restrict__ bits_out, void* shed_out, const ShedDev& sdv,
+                                           uint32_t* s_cnt, float dt, float& lmax, HubCtx& H)
 {
-    if constexpr (CU == 1) {
-        // one chunk per pass holds at most 64 items: packing would still
-        // evaluate f once, so evaluate it on the flagged lanes in place
-        (void)xch;
-        (void)lane;
-        if (flag[0]) result[0] = f(payload[0]);
-        return;
+    using state_t = typename Store<STORAGE>::state_t;
+    using age_t = typename Store<STORAGE>::age_t;
+    // (the queue was written by other lanes of this wavefront)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    Q.n -= m;
+    const uint32_t R = 1u << a.lgR;
+    bool fire = false;
+    uint32_t unit = 0, x = 0;
+    if (lane < m) {
+        const uint2 e = Q.q[Q.n + lane];
+        x = (e.y >> 29) & 3u;
+        uint32_t c = Q.wave + ((e.y & 0x1FFFFFFFu) >> 6) * Q.nwaves;
+        if (EXTRA && a.act) c = a.act[2 + c];
+        unit = (c << 6) + (e.y & 63u);
+        const uint32_t id = UNIFORM ? unit >> a.lgR : (uint32_t)opaque_uniform(a.orig_id)[unit >> a.lgR];
+        float lam = __uint_as_float(e.x);
+        if (e.y & DRAW_EVAL) {
+            lam = unit_hazard(a.hz_dev, a.same_kind, lam, x == (uint32_t)ST_I);
+            if (EXTRA && a.rates) a.rates[unit] = lam;
+            lmax = fmaxf(lmax, lam);
+        }
+        // the key and step pass through an empty asm here, so the round keys
+        // and the key-step terms are formed by scalar adds at each draw
+        // instead of being hoisted out of the walk, where they would take 20
+        // scalar registers and be spilled to vector lanes
+        uint32_t k0 = __builtin_amdgcn_readfirstlane(a.key0), k1 = __builtin_amdgcn_readfirstlane(a.key1),
+                 ks = __builtin_amdgcn_readfirstlane(k);
+        asm volatile("" : "+s"(k0), "+s"(k1), "+s"(ks));
+        const uint32_t w = fsd::philox4x32_10(make_uint4(id, ks, unit & (R - 1), 0u), k0, k1).x >> 8;
+        fire = fsd::bernoulli((float)w * 0x1p-24f, lam * dt);
     }
-    unsigned long long m[CU];
-    uint32_t pre[CU + 1];
-    pre[0] = 0;
-#pragma unroll
-    for (int u = 0; u < CU; ++u) {
-        m[u] = __ballot(flag[u]);
-        pre[u + 1] = pre[u] + (uint32_t)__popcll(m[u]);
+    if (__ballot(fire) == 0ull) return;
+    if (fire) {
+        opaque_uniform((state_t*)a.state)[unit] = (state_t)(x + 1u);
+        opaque_uniform((age_t*)a.age)[unit] = (age_t)0;
+        atomicAdd(&s_cnt[(unit & (R - 1)) * 4u + x], 1u); // LDS
+        if (x != (uint32_t)ST_S)
+            __hip_atomic_fetch_xor(&bits_out[unit >> 5], 1u << (unit & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (SHED && x == (uint32_t)ST_E) {
+            // newly infectious: s at age 0
+            const float v = fsd::shed(sdv, 0.0f);
+            if (STORAGE == 0) ((float*)shed_out)[unit] = v;
+            else ((uint16_t*)shed_out)[unit] = (uint16_t)float_to_half_bits(v);
+        }
     }
-    const uint32_t total = pre[CU];
-    const unsigned long long lt = (1ull << lane) - 1ull;
-    uint32_t slot[CU];
-#pragma unroll
-    for (int u = 0; u < CU; ++u) slot[u] = pre[u] + (uint32_t)__popcll(m[u] & lt);
-    for (uint32_t r0 = 0; r0 < total; r0 += 64) {
-#pragma unroll
-        for (int u = 0; u < CU; ++u)
-            if (flag[u] && slot[u] >= r0 && slot[u] < r0 + 64) xch[slot[u] - r0] = payload[u];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (r0 + lane < total) xch[lane] = f(xch[lane]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int u = 0; u < CU; ++u)
-            if (flag[u] && slot[u] >= r0 && slot[u] < r0 + 64) result[u] = xch[slot[u] - r0];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (HUBS && H.on) {
+        // a unit entering or leaving I is queued for its pushes into the
+        // next step's deltas of the binned rows that list its node
+        const bool push = fire && x != (uint32_t)ST_S;
+        const unsigned long long pm = __ballot(push);
+        if (pm != 0ull) {
+            const uint32_t cnt = (uint32_t)__popcll(pm);
+            if (H.n + cnt > PUSHQ) flush_pushes(a, H, lane);
+            if (push)
+                H.q[H.n + (uint32_t)__popcll(pm & ((1ull << lane) - 1ull))] =
+                    unit | (x == (uint32_t)ST_I ? 0x80000000u : 0u);
+            H.n += cnt;
+        }
     }
 }
 
-// Everything of one pass after its loads were issued: rates (gather,
-// hazards), draws, stores, next-infectivity words (and, with SHED, the
-// s(tau') values of the units infectious after the step), counts, and the
-// chunk's live flag for compaction.
+// Everything of one pass after its loads were issued but the draws: rates
+// (gather, hazards), the ages and infectivity words of the units that do not
+// fire, (with SHED) the next s(tau) of the infectious units, the queue of the
+// draws, and the chunk's live flag for compaction.
 template <int STORAGE, bool WEIGHTED, int MODE, int UD, bool SHED, bool EXTRA, int PB, class age_t>
 __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t>& P, uint32_t lane,
                                              const uint32_t* __restrict__ s_bits, rsrc_t gbits, rsrc_t shedr,
                                              void* __restrict__ shed_out, const ShedPre& sv, const ShedDev& sdv,
-                                             uint32_t* xch, unsigned long long k,
-                                             unsigned long long* __restrict__ bits_out, uint32_t* s_cnt,
-                                             uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3, float dt,
-                                             float& lmax, HubCtx& H)
+                                             unsigned long long* __restrict__ bits_out, float dt, float& lmax,
+                                             const HubCtx& H, DrawCtx& Q)
 {
     constexpr bool UNIFORM = UD != 0;
-    using state_t = typename Store<STORAGE>::state_t;
     const uint32_t R = 1u << a.lgR;
-
-    // the pass's loaded words; lanes past the chunk's valid units act as R
-    bool valid[CU];
-    int x[CU];
-    age_t ag[CU];
-    uint32_t dg[CU], unit[CU];
 #pragma unroll
     for (int u = 0; u < CU; ++u) {
-        valid[u] = lane < P.nvalid[u];
-        unit[u] = (P.chk[u] << 6) + lane;
-        x[u] = valid[u] ? (int)P.xr[u] : ST_R;
-        ag[u] = valid[u] ? age_from_raw<age_t>(P.agw[u]) : (age_t)0;
-        dg[u] = valid[u] ? P.dgr[u] : 0u;
-    }
+        // the pass's loaded words; lanes past the chunk's valid units act as R
+        const bool valid = lane < P.nvalid[u];
+        const uint32_t u0 = P.chk[u] << 6, unit = u0 + lane;
+        const int x = valid ? (int)P.xr[u] : ST_R;
+        const age_t ag = valid ? age_from_raw<age_t>(P.agw[u]) : (age_t)0;
+        const uint32_t dg = valid ? P.dgr[u] : 0u;
 
-    // 1.-2. rate: beta * pressure for S; hazard at the start-of-step age for E/I; 0 for R
-    float lam[CU];
-#pragma unroll
-    for (int u = 0; u < CU; ++u) {
-        lam[u] = 0.0f;
-        const bool heavy = !UNIFORM && dg[u] == HEAVY_ROW;
-        const bool want = x[u] == ST_S && !heavy;
+        // 1.-2. rate: beta * pressure for S; hazard at the start-of-step age
+        // for E/I; 0 for R
+        float lam = 0.0f;
+        const bool heavy = !UNIFORM && dg == HEAVY_ROW;
+        const bool want = x == ST_S && !heavy;
         const float p =
-            pressure_row<STORAGE, MODE, WEIGHTED, UD, SHED, PB>(a, P, u, want, dg[u], s_bits, gbits, shedr, sv, lane);
-        if (want) lam[u] = a.beta * p;
+            pressure_row<STORAGE, MODE, WEIGHTED, UD, SHED, PB>(a, P, u, want, dg, s_bits, gbits, shedr, sv, lane);
+        if (want) lam = a.beta * p;
         if (!UNIFORM && !WEIGHTED && !SHED && H.on) {
             // pushed pressure: every binned unit, whatever its state, carries
             // its count into this step's slot and clears the delta slot that
             // the next step's pushes do not use
             if (__ballot(heavy) != 0ull) {
-                const uint32_t h = heavy ? unit[u] - H.base : 0u;
+                const uint32_t h = heavy ? unit - H.base : 0u;
                 const uint32_t pp = P.ht[u] + P.hd[u];
                 st32(H.tr, heavy ? (H.t_cur + h) << 2 : OOB, pp);
                 st32(H.tr, heavy ? (H.d_clr + h) << 2 : OOB, 0u);
-                if (heavy && x[u] == ST_S) lam[u] = a.beta * (float)pp;
+                if (heavy && x == ST_S) lam = a.beta * (float)pp;
             }
-        } else if (!UNIFORM && heavy && x[u] == ST_S) {
-            lam[u] = a.beta * pressure_heavy<WEIGHTED || SHED>(a, unit[u] >> a.lgR, unit[u] & (R - 1));
+        } else if (!UNIFORM && heavy && x == ST_S) {
+            lam = a.beta * pressure_heavy<WEIGHTED || SHED>(a, unit >> a.lgR, unit & (R - 1));
         }
-    }
+        // the hazards of ages the table holds come from it; the others are
+        // evaluated with the draws
+        const bool ei = x == ST_E || x == ST_I;
+        const bool hit = (!UNIFORM || a.htab != nullptr) && ei && P.tab[u][0] == age_units(ag);
+        if (hit) lam = x == ST_I ? P.tab[u][2] : P.tab[u][1];
+        const bool miss = ei && !hit;
 
-    // hazards of the E/I units of the pass, on compacted lanes; the payload
-    // is the age bit pattern with bit 31 marking the I -> R law (ages are
-    // non-negative, so bit 31 is free)
-    {
-        bool need[CU];
-        uint32_t pay[CU], res[CU];
-#pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            need[u] = x[u] == ST_E || x[u] == ST_I;
-            pay[u] = age_bits(ag[u]) | (x[u] == ST_I ? 0x80000000u : 0u);
-            res[u] = 0;
-        }
-        // ages the table holds take their hazard from it
-        bool hit[CU];
-#pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            hit[u] = (!UNIFORM || a.htab != nullptr) && need[u] && P.tab[u][0] == age_units(ag[u]);
-            if (hit[u]) lam[u] = x[u] == ST_I ? P.tab[u][2] : P.tab[u][1];
-            need[u] = need[u] && !hit[u];
-        }
-        compact_apply<CU>(xch, lane, need, pay, res, [&](uint32_t w) {
-            return __float_as_uint(
-                unit_hazard(a.hz_dev, a.same_kind, age_from_bits<age_t>(w & 0x7FFFFFFFu), (w & 0x80000000u) != 0u));
-        });
-#pragma unroll
-        for (int u = 0; u < CU; ++u)
-            if (need[u]) lam[u] = __uint_as_float(res[u]);
-    }
+        // 3.-4. the draws (no draw at lambda = 0)
+        const bool need = miss || lam > 0.0f;
+        const unsigned long long nm = __ballot(need);
+        if (need)
+            Q.q[Q.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u))] =
+                make_uint2(__float_as_uint(miss ? age_units(ag) : lam),
+                           lane | (Q.pass << 6) | ((uint32_t)x << 29) | (miss ? DRAW_EVAL : 0u));
+        Q.n += (uint32_t)__popcll(nm);
+        lmax = fmaxf(lmax, lam);
 
-    // 3.-4. Bernoulli tau-leap: fire when u < 1 - exp(-lambda dt); no draw at
-    // lambda = 0.  The Philox draws of the pass run on compacted lanes.
-    bool fire[CU];
-    {
-        bool need[CU];
-        uint32_t pay[CU], res[CU];
-#pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            need[u] = lam[u] > 0.0f;
-            pay[u] = (P.org[u] << a.lgR) | (lane & (R - 1)); // the caller's node id and the replica
-            res[u] = 0;
-        }
-        const uint32_t kk = (uint32_t)k;
-        compact_apply<CU>(xch, lane, need, pay, res, [&](uint32_t un) {
-            // the key and step pass through an empty asm here, so the round
-            // keys and the key-step terms are formed by scalar adds at each
-            // draw instead of being hoisted out of the walk: held for the
-            // whole walk they would take 20 scalar registers and be spilled
-            // to vector lanes, each use a lane read
-            // (all three are wave-uniform)
-            uint32_t k0 = __builtin_amdgcn_readfirstlane(a.key0), k1 = __builtin_amdgcn_readfirstlane(a.key1),
-                     ks = __builtin_amdgcn_readfirstlane(kk);
-            asm volatile("" : "+s"(k0), "+s"(k1), "+s"(ks));
-            return fsd::philox4x32_10(make_uint4(un >> a.lgR, ks, un & (R - 1), 0u), k0, k1).x >> 8;
-        });
-#pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            fire[u] = false;
-            if (need[u]) {
-                const float uu = (float)res[u] * 0x1p-24f;
-                const float qq = -expm1f(-lam[u] * dt);
-                fire[u] = uu < qq;
-            }
-        }
-    }
-
-    int xns[CU];
-    age_t ans[CU];
-#pragma unroll
-    for (int u = 0; u < CU; ++u) {
-        // 5.-6. advance state and age in place (the chunk's descriptors drop
-        // the lanes past its valid units; the state only changes on a firing)
-        const int xn = x[u] + (fire[u] ? 1 : 0);
-        xns[u] = xn;
-        ans[u] = fire[u] ? (age_t)0 : age_next(ag[u], dt);
-        const uint32_t u0 = P.chk[u] << 6;
-        BufIO<state_t>::st(make_rsrc((state_t*)a.state + u0, P.nvalid[u] * sizeof(state_t)),
-                           fire[u] ? lane : OOB_ELEM, (uint32_t)xn);
-        BufIO<age_t>::st(make_rsrc((age_t*)a.age + u0, P.nvalid[u] * sizeof(age_t)), lane, age_to_raw(ans[u]));
-        lmax = fmaxf(lmax, lam[u]);
-        if (!UNIFORM && !WEIGHTED && !SHED && H.on) {
-            // a unit entering or leaving I is queued for its pushes into the
-            // next step's deltas of the binned rows that list its node
-            const bool push = fire[u] && (x[u] == ST_E || x[u] == ST_I);
-            const unsigned long long pm = __ballot(push);
-            if (pm != 0ull) {
-                const uint32_t cnt = (uint32_t)__popcll(pm);
-                if (H.n + cnt > PUSHQ) flush_pushes(a, H, lane);
-                if (push)
-                    H.q[H.n + (uint32_t)__popcll(pm & ((1ull << lane) - 1ull))] =
-                        unit[u] | (x[u] == ST_I ? 0x80000000u : 0u);
-                H.n += cnt;
-            }
-        }
+        // 5.-6. the age of a unit that does not fire (the chunk's descriptors
+        // drop the lanes past its valid units)
+        const age_t an = age_next(ag, dt);
+        BufIO<age_t>::st(make_rsrc((age_t*)a.age + u0, P.nvalid[u] * sizeof(age_t)), lane, age_to_raw(an));
         // the rates, when recorded (EXTRA kernels)
-        if (EXTRA && a.rates) st32(make_rsrc(a.rates + u0, P.nvalid[u] * 4u), lane << 2, __float_as_uint(lam[u]));
+        if (EXTRA && a.rates) st32(make_rsrc(a.rates + u0, P.nvalid[u] * 4u), lane << 2, __float_as_uint(lam));
         // 7. next-step infectivity bits (one 64-bit word per chunk, written by
-        // lanes 0 and 1) and 8. counts
-        const unsigned long long mI = __ballot(valid[u] && xn == ST_I);
+        // lanes 0 and 1)
+        const unsigned long long mI = __ballot(valid && x == ST_I);
         if (UNIFORM) {
             st32(make_rsrc(bits_out + P.chk[u], P.live[u] ? 8u : 0u), lane < 2 ? lane << 2 : OOB,
                  lane == 0 ? (uint32_t)mI : (uint32_t)(mI >> 32));
@@ -1070,47 +1025,31 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
             // (mixed layouts: bits_out is held in vector registers)
             ((uint32_t*)bits_out)[2 * P.chk[u] + lane] = lane == 0 ? (uint32_t)mI : (uint32_t)(mI >> 32);
         }
-        if (R == 1) {
-            c0 += (uint32_t)__popcll(__ballot(valid[u] && xn == ST_S));
-            c1 += (uint32_t)__popcll(__ballot(valid[u] && xn == ST_E));
-            c2 += (uint32_t)__popcll(mI);
-            c3 += (uint32_t)__popcll(__ballot(valid[u] && xn == ST_R));
-        } else if (valid[u]) {
-            atomicAdd(&s_cnt[(unit[u] & (R - 1)) * 4 + xn], 1u); // LDS
-        }
         // compaction: whether the chunk held a unit that is not R at the start
         // of the step.  A chunk is dropped only after a step that began with
         // all its units in R, so both of its ping-pong bitmap words are 0
         // (it held no I unit before or after that step) and stay 0.
         if (EXTRA && a.live) {
-            const bool alive = __ballot(valid[u] && x[u] != ST_R) != 0ull;
+            const bool alive = __ballot(valid && x != ST_R) != 0ull;
             __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(alive ? 1 : 0),
                                                  make_rsrc(a.live + P.chk[u], P.live[u] ? 1u : 0u),
                                                  lane == 0 ? 0 : (int)OOB, 0, 0);
         }
-    }
-
-    if (SHED) {
-        // 7'. infectivity values s(tau') of the units infectious after the
-        // step (Eq. (infectivity)), on compacted lanes (a separate round
-        // measured faster than folding s(tau + dt) into the hazard round)
-        bool need[CU];
-        uint32_t pay[CU], res[CU];
-#pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            need[u] = valid[u] && xns[u] == ST_I;
-            pay[u] = age_bits(ans[u]);
-            res[u] = 0;
-        }
-        compact_apply<CU>(xch, lane, need, pay, res, [&](uint32_t w) {
-            return __float_as_uint(fsd::shed(sdv, age_from_bits<age_t>(w)));
-        });
-#pragma unroll
-        for (int u = 0; u < CU; ++u)
-            shed_put<STORAGE>(make_rsrc((char*)shed_out + (size_t)(P.chk[u] << 6) * Store<STORAGE>::shed_bytes,
+        if (SHED) {
+            // 7'. infectivity values s(tau') of the units that stay infectious
+            // (Eq. (infectivity))
+            const bool inf = valid && x == ST_I;
+            float v = 0.0f;
+            if (inf) {
+                v = fsd::shed(sdv, age_units(an));
+                asm volatile("" : "+v"(v)); // (no pending load leaves the branch)
+            }
+            shed_put<STORAGE>(make_rsrc((char*)shed_out + (size_t)u0 * Store<STORAGE>::shed_bytes,
                                         P.nvalid[u] * Store<STORAGE>::shed_bytes),
-                              lane, need[u], __uint_as_float(res[u]));
+                              lane, inf, v);
+        }
     }
+    ++Q.pass;
 }
 
 // One fused step.  Units are processed in chunks of 64 (one wavefront, one
@@ -1136,13 +1075,15 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     __shared__ uint32_t s_cnt[4 * 64];
     __shared__ __attribute__((aligned(16))) uint32_t s_bits[USE_LDS ? RESIDENT_BITS / 32 : 4];
     static_assert(SUMMARY_BITS <= RESIDENT_BITS, "the summary shares the LDS bitmap array");
-    __shared__ uint32_t s_xch[NW][64];
+    __shared__ uint2 s_draw[NW][DRAWQ];
     // pushed pressure of binned rows: per-wavefront push queue and flush tables
     constexpr bool HUBS = !UNIFORM && !WEIGHTED && !SHED;
     __shared__ uint32_t s_pq[HUBS ? NW : 1][HUBS ? PUSHQ : 1];
     __shared__ uint32_t s_pb[HUBS ? NW : 1][HUBS ? 64 : 1];
+    __shared__ uint32_t s_px[HUBS ? NW : 1][HUBS ? 64 : 1];
 
-    const uint32_t tid = threadIdx.x;
+    // (a workgroup of the LDS variants may have fewer threads than TPB)
+    const uint32_t tid = threadIdx.x, tpb = USE_LDS ? blockDim.x : (uint32_t)TPB, nw = tpb / 64;
     const uint32_t lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform, in a scalar register
     const uint32_t R = 1u << a.lgR;
@@ -1169,14 +1110,14 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         dt = fminf(a.dt, a.eps / (m + a.delta));
     }
     float lmax = 0.0f;
-    const uint32_t wave_id = block * NW + wave;
-    const uint32_t nwaves = nblocks * NW;
+    const uint32_t wave_id = block * nw + wave;
+    const uint32_t nwaves = nblocks * nw;
     HubCtx H;
     H.on = HUBS && a.hub_T != nullptr;
     H.n = 0;
     H.q = s_pq[HUBS ? wave : 0];
     H.pb = s_pb[HUBS ? wave : 0];
-    H.px = s_xch[wave];
+    H.px = s_px[HUBS ? wave : 0];
     H.t_prev = H.t_cur = H.d_cur = H.d_clr = H.d_next = H.base = 0;
     if (H.on) {
         const uint32_t HU = a.hub_units;
@@ -1210,22 +1151,21 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         }
     }
     issue_pass<STORAGE, UD, EXTRA, PB>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
-    if (R > 1)
-        for (uint32_t i = tid; i < 4 * R; i += TPB) s_cnt[i] = 0;
+    for (uint32_t i = tid; i < 4 * R; i += tpb) s_cnt[i] = 0;
     if (USE_LDS) {
         // 16 bytes per lane straight into LDS: wave w fills the blocks of 64
         // uint4 it owns; lane l's block element lands at base + 16 l
         const uint32_t nbits = MODE == MODE_RESIDENT ? total : a.sum_bits;
         const uint32_t n4 = (((nbits + 31) >> 5) + 3) >> 2;
         const uint4* src = (const uint4*)(MODE == MODE_RESIDENT ? bits_in : a.summary);
-        for (uint32_t b0 = wave * 64; b0 < n4; b0 += TPB) {
+        for (uint32_t b0 = wave * 64; b0 < n4; b0 += tpb) {
             if (b0 + lane < n4)
                 __builtin_amdgcn_global_load_lds((const void*)(src + b0 + lane),
                                                  (__attribute__((address_space(3))) void*)((uint4*)s_bits + b0), 16, 0, 0);
         }
         __builtin_amdgcn_s_waitcnt(0);
     }
-    if (R > 1 || USE_LDS) __syncthreads();
+    __syncthreads();
     TabRef tv{nullptr, 0.0f, 0.0f};
     if (!UNIFORM) {
         tv.p = in_vgpr(a.htab);
@@ -1247,7 +1187,14 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     }
     issue_table<UNIFORM>(a, tv, P, lane);
 
-    uint32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0; // per-wave counts (R == 1)
+    DrawCtx Q{s_draw[wave], 0u, 0u, wave_id, nwaves};
+    // whole wavefronts of draws, and after the wavefront's last pass the rest
+    auto draws = [&](bool last) {
+        while (Q.n >= (last ? 1u : 64u))
+            draw_batch<STORAGE, UNIFORM, SHED, EXTRA, HUBS>(a, Q, min(Q.n, 64u), lane, (uint32_t)k, (uint32_t*)bo,
+                                                            shed_out, sdv, s_cnt, dt, lmax, H);
+    };
+    static_assert(CU == 1, "walk position of a queued draw: one chunk per pass");
 
     // passes: the loads of the next pass are issued (always: a pass past the
     // end reads nothing) before the current pass is processed; two register
@@ -1264,9 +1211,9 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
             issue_pass<STORAGE, UD, EXTRA, PB>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P1,
                                                 ahead, H);
         process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB>(a, P, lane, s_bits, gbits, shedr, shed_out, sv,
-                                                                    sdv, s_xch[wave], k, bo, s_cnt, c0, c1, c2,
-                                                                    c3, dt, lmax, H);
+                                                                    sdv, bo, dt, lmax, H, Q);
         first += stride;
+        draws(first >= walk);
         if (first >= walk) break;
         if (!PREFETCH)
             issue_pass<STORAGE, UD, EXTRA, PB>(a, first, nwaves, stride, nchunks, walk, total, lane, P1, ahead, H);
@@ -1276,9 +1223,9 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
             issue_pass<STORAGE, UD, EXTRA, PB>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P,
                                                 ahead, H);
         process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB>(a, P1, lane, s_bits, gbits, shedr, shed_out, sv,
-                                                                    sdv, s_xch[wave], k, bo, s_cnt, c0, c1, c2,
-                                                                    c3, dt, lmax, H);
+                                                                    sdv, bo, dt, lmax, H, Q);
         first += stride;
+        draws(first >= walk);
         if (!PREFETCH && first < walk)
             issue_pass<STORAGE, UD, EXTRA, PB>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
         if (first < walk) issue_table<UNIFORM>(a, tv, P, lane);
@@ -1288,28 +1235,11 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     // in flight any more)
     if (H.on && H.n > 0) flush_pushes(a, H, lane);
 
-    // one plain store of this workgroup's counts; the reduce kernel sums them
-    // (workgroup 0 also counts the R units of the chunks compaction skipped)
+    // one plain store of this workgroup's transitions; the reduce kernel adds
+    // their sums to the counts before the step
     uint32_t* out = a.part + ((size_t)a.step_off * nblocks + block) * (4 * R);
-    const uint32_t skipped = (EXTRA && a.act && block == 0) ? a.act[1] : 0u;
-    if (R == 1) {
-        if (lane == 0) {
-            s_cnt[wave * 4 + 0] = c0;
-            s_cnt[wave * 4 + 1] = c1;
-            s_cnt[wave * 4 + 2] = c2;
-            s_cnt[wave * 4 + 3] = c3;
-        }
-        __syncthreads();
-        if (tid < 4) {
-            uint32_t t = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) t += s_cnt[w * 4 + tid];
-            out[tid] = t + (tid == ST_R ? skipped : 0u);
-        }
-    } else {
-        __syncthreads();
-        for (uint32_t i = tid; i < 4 * R; i += TPB) out[i] = s_cnt[i] + ((i & 3) == ST_R ? skipped : 0u);
-    }
+    __syncthreads();
+    for (uint32_t i = tid; i < 4 * R; i += tpb) out[i] = s_cnt[i];
     if (a.adaptive) {
         // the workgroup's largest rate, for the next step's size; block 0
         // records this step's size
@@ -1319,8 +1249,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         __syncthreads();
         if (tid == 0) {
             float m = 0.0f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) m = fmaxf(m, s_lmax[w]);
+            for (uint32_t w = 0; w < nw; ++w) m = fmaxf(m, s_lmax[w]);
             a.lam_part[(size_t)(k & 1) * nblocks + block] = m;
             if (block == 0) a.dt_hist[k % a.hist_len] = dt;
         }
