@@ -192,8 +192,9 @@ typedef struct fs_sim_params {
                                 <= 2^20), 3 = summary (an LDS summary with one bit per
                                 group of units screens the bitmap reads), 0 = automatic:
                                 resident when it fits, else summary for adaptive steps,
-                                bitmaps over 8 MB, or uniform-degree graphs with at most
-                                4 replicas, else streaming.  Results are identical. */
+                                bitmaps over 8 MB, uniform-degree graphs with at most
+                                4 replicas, or unit weights with at most 2, else
+                                streaming.  Results are identical. */
     int32_t heavy_degree;    /* degree bins: rows with more incoming edges than this get
                                 their pressure from the heavy-row kernel (segments of
                                 segment_edges edges, one wavefront each); 0 = 64,
@@ -500,7 +501,8 @@ fs_status fs_markov_history(fs_markov* m, int64_t first_step, int64_t n, int64_t
  * gets alone (same draws, same states, same counts).  Small simulations that
  * cannot fill the GPU alone fill it together.
  *
- * Members must be created with variant = 1 (streaming step), the batch's
+ * Members must be created with variant = 1 (streaming step; an automatic
+ * choice of the summary for a graph of mixed degrees becomes it), the batch's
  * storage, and agree on weights (all weighted or none) and record_rates.
  * While a sim belongs to a batch, its device work runs on the batch's stream:
  * fs_counts, fs_history, fs_get_state, fs_set_state, fs_get_rates and

@@ -202,18 +202,18 @@ fs_status rebuild_tables(fs_batch* b)
 // streaming step of the batch's storage with fixed steps, constant shedding
 // and no compaction, and the members agree on weights (the batch kernel is
 // instantiated for one of the two).
-fs_status member_check(const fs_batch* b, const fs_sim* s, bool allow_packed = false)
+fs_status member_check(const fs_batch* b, const fs_sim* s, bool joining = false)
 {
     if (s->batch) return fail(FS_ERR_BUSY, "sim already belongs to a batch");
     if (s->device != b->device) return fail(FS_ERR_INVALID_ARG, "sim and batch are on different devices");
-    if (s->mode != fsi::MODE_STREAM)
+    if (s->mode != fsi::MODE_STREAM && !(joining && s->stream_too))
         return fail(FS_ERR_INVALID_ARG, "batch members run the streaming step: create the sim with variant = 1");
     if (s->storage != b->storage) return fail(FS_ERR_INVALID_ARG, "sim storage differs from the batch's");
     if (s->p.adaptive) return fail(FS_ERR_INVALID_ARG, "adaptive-step sims cannot join a batch");
     if (s->p.shedding != FS_SHED_CONSTANT)
         return fail(FS_ERR_INVALID_ARG, "sims with age-dependent shedding cannot join a batch");
     if (s->p.compaction) return fail(FS_ERR_INVALID_ARG, "sims with compaction cannot join a batch");
-    if (!allow_packed && s->layout && s->layout->pbits != 0)
+    if (!joining && s->layout && s->layout->pbits != 0)
         return fail(FS_ERR_INVALID_ARG, "batch members read 32-bit columns (the sim has packed ones)");
     const int w = s->g->d_weights != nullptr;
     if (!b->members.empty() && w != b->weighted)
@@ -353,6 +353,8 @@ fs_status fs_batch_add(fs_batch* b, fs_sim* s)
     // the batch kernel reads 32-bit columns: a sim with packed ones moves to
     // the graph's layout with plain columns first
     if ((st = use_plain_columns(s)) != FS_OK) return st;
+    // a sim whose automatic variant is the summary joins with the streaming step
+    if ((st = apply_variant(s, fsi::MODE_STREAM)) != FS_OK) return st;
     return attach(b, s);
     FS_GUARD_END
 }

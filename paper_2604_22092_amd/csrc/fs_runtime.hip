@@ -1062,7 +1062,9 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     if (tp.cache_path) {
         int mode = 0;
         int32_t hd = 0, se = 0;
-        if (cache_lookup(tp.cache_path, out->signature, &mode, &hd, &se) && (tp.variants || mode == s->mode)) {
+        if (cache_lookup(tp.cache_path, out->signature, &mode, &hd, &se) &&
+            (tp.variants || mode == s->mode || (s->stream_too && mode == fsi::MODE_STREAM))) {
+            if (tp.variants) s->stream_too = false;
             FS_HIP(hipStreamSynchronize(s->stream));
             fs_status st = apply_variant(s, mode);
             if (st == FS_OK) st = apply_bins(s, hd, se);
@@ -1184,6 +1186,7 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     if ((st = apply_bins(s, best.first, best.second)) != FS_OK) return st;
     FS_HIP(refresh_summary(s));
     FS_HIP(hipStreamSynchronize(s->stream));
+    if (tp.variants) s->stream_too = false;
     out->variant = s->mode + 1;
     out->heavy_degree = s->heavy_deg;
     out->segment_edges = s->seg_edges;
@@ -1434,13 +1437,25 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
         release_sim(s);
         return fail(FS_ERR_INVALID_ARG, "the resident variant holds at most 2^20 units (n * n_replicas)");
     }
-    // automatic choice (measured on MI355X): the LDS bitmap when it fits; else
-    // the LDS summary for adaptive steps, for bitmaps beyond 8 MB (the
-    // summary screens random reads that would miss the L2), and for
-    // uniform-degree graphs with at most 4 replicas; else the streaming
-    // variant, whose higher occupancy wins once replicas share bitmap words
+    // automatic choice (us per step, streaming / summary): the LDS bitmap when
+    // it fits; else the LDS summary
+    //  - for adaptive steps (which need an LDS variant);
+    //  - for bitmaps beyond 8 MB (it screens random reads that would miss the L2);
+    //  - for uniform-degree graphs with at most 4 replicas;
+    //  - for unit weights with one or two replicas, whose gathers mostly find an
+    //    empty group also where a quarter of the units is infectious (Erdos-Renyi
+    //    8, N = 1.2e6 42 / 23 with few infectious units, 42 / 29 with many, N =
+    //    3e6 103 / 36 and 101 / 51; Barabasi-Albert 4, N = 3e6 103 / 60 and 95 /
+    //    65; Erdos-Renyi 8, N = 1e6, R = 2 52 / 28 and 52 / 33; with shedding, N =
+    //    1.1e6 44 / 42, with compaction, Barabasi-Albert 4, N = 1.1e6 44 / 43);
+    // else the streaming variant: weighted rows gather binned rows as float
+    // partials and read a weight per edge whatever the summary says
+    // (Barabasi-Albert 5, N = 1.1e6 55 / 60), and once more replicas share
+    // bitmap words few groups are empty and its higher occupancy wins.
     const bool uniform = g->min_degree == g->max_degree && g->max_degree <= fsi::UNIFORM_MAX_DEG;
-    const bool summary_auto = p->adaptive || bitmap_words(units) * 8 > ((size_t)8 << 20) || (uniform && R <= 4);
+    const bool summary_large = p->adaptive || bitmap_words(units) * 8 > ((size_t)8 << 20) || (uniform && R <= 4);
+    const bool summary_auto = summary_large || (R <= 2 && !g->d_weights);
+    s->stream_too = p->variant == 0 && !fits_lds && !summary_large;
     s->mode = p->variant == 1 ? fsi::MODE_STREAM
             : p->variant == 2 ? fsi::MODE_RESIDENT
             : p->variant == 3 ? fsi::MODE_SUMMARY

@@ -91,6 +91,7 @@ struct fs_sim {
     int storage = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    bool stream_too = false; // automatic variant: a batch may switch it to the streaming step
     void* d_state = nullptr;
     void* d_age = nullptr;
     void* d_iota[2] = {nullptr, nullptr};
@@ -248,5 +249,7 @@ void graph_closed();
 // 32-bit columns (the batch kernel reads only those); the sim's stream must
 // be idle.  Results do not change.
 fs_status use_plain_columns(fs_sim* s);
+// Switches a sim to another step variant (a fsi::MODE_); its stream must be idle.
+fs_status apply_variant(fs_sim* s, int mode);
 
 } // namespace fsr
