@@ -7,24 +7,24 @@
 namespace fsk {
 
 template <int STORAGE, int LGW>
-__global__ __launch_bounds__(REPS_TPB, 4) void reps_kernel(StepArgs a)
+__global__ __launch_bounds__(REPS_TPB, reps_waves(LGW)) void reps_kernel(StepArgs a)
 {
     __shared__ RepsShared<LGW> s;
-    reps_body<STORAGE, LGW>(a, s, blockIdx.x, gridDim.x);
+    // (the first and only argument)
+    reps_body<STORAGE, LGW>((ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(), a.step_off, s, blockIdx.x, gridDim.x);
 }
 
 // Every member of a batch that runs the replica step with groups of 2^LGW
 // chunks: member m owns the workgroups [first[m], first[m + 1]).
 template <int STORAGE, int LGW>
-__global__ __launch_bounds__(REPS_TPB, 4) void reps_batch_kernel(const StepArgs* __restrict__ table,
+__global__ __launch_bounds__(REPS_TPB, reps_waves(LGW)) void reps_batch_kernel(const StepArgs* __restrict__ table,
                                                               const uint32_t* __restrict__ first, uint32_t members,
                                                               uint32_t step_off)
 {
     __shared__ RepsShared<LGW> s;
     const uint32_t m = owner_of(first, members, blockIdx.x);
-    StepArgs a = table[m];
-    a.step_off = step_off;
-    reps_body<STORAGE, LGW>(a, s, blockIdx.x - first[m], first[m + 1] - first[m]);
+    reps_body<STORAGE, LGW>((ArgsPtr)(unsigned long long)(table + m), step_off, s, blockIdx.x - first[m],
+                            first[m + 1] - first[m]);
 }
 
 template <int S>

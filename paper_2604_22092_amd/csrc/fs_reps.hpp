@@ -21,7 +21,7 @@
 // Measured (traced step launches, one MI355X): Barabasi-Albert m = 4, N = 3e5,
 // 16 replicas, FP32 56.0 -> 33.3 us (89 vector instructions per chunk); m = 5,
 // N = 1e6, 16 replicas 172 -> 88 us; Erdos-Renyi mean degree 10, N = 3e4, 64
-// replicas 25.8 -> 12.8 us.  What is left there is the latency of the chain
+// replicas 25.8 -> 12.5 us.  What is left there is the latency of the chain
 // columns -> bits -> bytes -> units (5 of 14 us of a wavefront's life in the
 // gather, one L1 lookup per edge and compute unit and cycle) and, at N = 1e6,
 // the state and age traffic.
@@ -34,10 +34,15 @@ namespace fsk {
 // Rows have at most REPS_MAX_DEG light edges: seven planes hold the count, and
 // it fits the unit's byte.
 constexpr uint32_t REPS_TPB = STREAM_TPB;
-// Chunks whose loads are in flight together, and queued draws: at most 63 left
-// over plus every unit of those chunks.
-constexpr int REPS_NS = 4;
-constexpr uint32_t REPS_QCAP = 64 + REPS_NS * 64;
+// Chunks whose loads are in flight together, and wavefronts per SIMD, by group
+// width.  Groups of 4 and of 8 chunks fit 96 vector registers with few spills or
+// none, so five wavefronts share a SIMD: the 5000 groups of regular d = 6, N =
+// 2e4, R = 64 run at once (compact, 11.3 us per step with four, 9.3 with five).
+// Groups of 16 need the four chunks' loads in flight more (Barabasi-Albert 4, N =
+// 3e5, R = 16: 33.7 us, two chunks and five wavefronts 35.2).  Draws queued: at
+// most 63 left over plus every unit of those chunks.
+constexpr int reps_ns(int lgw) { return lgw == 3 ? 2 : 4; }
+constexpr int reps_waves(int lgw) { return lgw == 4 ? 4 : 5; }
 // Queue entry: the unit in its group (10 bits), its state, and whether the
 // first word is the age of a unit whose hazard is yet to be evaluated.
 constexpr uint32_t REPS_EVAL = 0x80000000u;
@@ -48,7 +53,7 @@ struct RepsShared {
     static constexpr int NW = REPS_TPB / 64;
     uint32_t cnt[4 * 64];          // transitions per (replica, compartment left)
     uint32_t press[NW][16 * W];    // one byte per unit of the group
-    uint2 q[NW][REPS_QCAP];        // (rate or age, unit in the group | state << 10 | REPS_EVAL)
+    uint2 q[NW][64 + reps_ns(LGW) * 64];        // (rate or age, unit in the group | state << 10 | REPS_EVAL)
     uint32_t id[NW][64];           // the caller's node id of each gather lane
     uint32_t flip[NW][2 * W];      // infectivity bits changed by the draws
     uint32_t pq[NW][PUSHQ];        // pushes of binned rows
@@ -95,14 +100,37 @@ __device__ __forceinline__ uint32_t block_bits(rsrc_t gbits, uint32_t col, int32
     return __builtin_amdgcn_ubfe(v, b & 7u, 1u << LGW);
 }
 
-template <int STORAGE, int LGW>
-__device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S, uint32_t block, uint32_t nblocks)
+// The launch's arguments in constant memory.  Narrow groups read them in every
+// part of the step through a pointer the compiler cannot follow (fresh_args), so
+// it loads what the part uses there instead of holding all of them from the
+// start on, spilled to vector lanes (73 of them, now 18).  With groups of 16 the
+// later loads cost more than the spills (Barabasi-Albert 5, N = 1e6, R = 16: 87.8
+// us held, 89.4 read anew).
+typedef const __attribute__((address_space(4))) StepArgs* ArgsPtr;
+template <int LGW>
+__device__ __forceinline__ ArgsPtr fresh_args(ArgsPtr p)
 {
+    if (LGW < 4) asm volatile("" : "+s"(p));
+    return p;
+}
+
+// The lane's number, formed where it is asked for: neither it nor an address
+// formed from it is held through the whole walk.
+__device__ __forceinline__ uint32_t fresh_lane()
+{
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, in_vgpr(0u)));
+}
+
+template <int STORAGE, int LGW>
+__device__ __forceinline__ void reps_body(ArgsPtr args, uint32_t step_off, RepsShared<LGW>& S, uint32_t block,
+                                          uint32_t nblocks)
+{
+    const auto& a = *args;
     using state_t = typename Store<STORAGE>::state_t;
     using age_t = typename Store<STORAGE>::age_t;
     constexpr uint32_t W = 1u << LGW;
     constexpr int NW = RepsShared<LGW>::NW;
-    constexpr int NS = REPS_NS;
+    constexpr int NS = reps_ns(LGW);
     constexpr int SUBS = (int)W / NS;
     static_assert(W >= NS, "a group holds at least one sub-batch");
 
@@ -126,15 +154,7 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
 
     uint32_t qn = 0; // queued draws (wave-uniform)
 
-    // The step index comes by a vector load issued with the first group's: as
-    // a scalar load, every scalar wait before it is needed would wait for it.
-    const rsrc_t ctr = make_rsrc(a.ctl, 8u);
-    uint32_t ctl_lo = ld32(ctr, 0u), ctl_hi = ld32(ctr, 4u);
-    bool first = true;
-    unsigned long long k = 0;
     uint32_t kk = 0;
-    rsrc_t gbits = tabr;
-    unsigned long long* __restrict__ bits_out = nullptr;
     HubCtx H;
     H.on = a.hub_T != nullptr;
     H.n = 0;
@@ -148,10 +168,9 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
     // the densest rows of a degree-sorted order come last: taken first, they
     // do not make the launch's tail
     for (uint32_t g0 = block * NW + wave; g0 < ngroups; g0 += nblocks * NW) {
+        const auto& a = *fresh_args<LGW>(args);
         const uint32_t g = __builtin_amdgcn_readfirstlane(ngroups - 1u - g0);
-        // (opaque here, so that no address formed from it is held through the
-        // whole walk of a few groups)
-        const uint32_t lane = in_vgpr(lane0);
+        const uint32_t lane = fresh_lane();
         const uint32_t q = lane >> lgNB;
         const uint32_t rep0 = (lane & ((1u << lgNB) - 1u)) << LGW;
         const uint32_t u0 = g << (6 + LGW);
@@ -170,6 +189,9 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
             xs[i] = BufIO<state_t>::ld(str, (uint32_t)i * 64u + lane);
             as[i] = BufIO<age_t>::ld(agr, (uint32_t)i * 64u + lane);
         }
+        // (the step index too, by a vector load: every scalar wait before it is
+        // needed would wait for a scalar one)
+        const auto ctl = __builtin_amdgcn_raw_buffer_load_b64(make_rsrc(a.ctl, 8u), 0, 0, 0);
         uint32_t base, ud;
         uint32_t id = node;
         uint32_t d = 0; // this lane's light edges
@@ -235,22 +257,20 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
                 tI[i] = __uint_as_float(t[2]);
             }
         };
-        if (first) {
-            first = false;
-            k = (((unsigned long long)__builtin_amdgcn_readfirstlane(ctl_hi) << 32) |
-                 __builtin_amdgcn_readfirstlane(ctl_lo)) + a.step_off;
-            kk = (uint32_t)k;
-            gbits = make_rsrc((k & 1) ? a.iota1 : a.iota0, ((total + 511u) >> 9) << 6);
-            bits_out = (unsigned long long*)((k & 1) ? a.iota0 : a.iota1);
-            if (H.on) {
-                const uint32_t HU = a.hub_units;
-                const uint32_t k2 = (uint32_t)(k & 1ull), k3 = (uint32_t)(k % 3ull);
-                H.t_prev = in_vgpr((k2 ^ 1u) * HU);
-                H.t_cur = in_vgpr(k2 * HU);
-                H.d_cur = in_vgpr((2u + k3) * HU);
-                H.d_next = in_vgpr((2u + (k3 + 1u) % 3u) * HU);
-                H.d_clr = in_vgpr((2u + (k3 + 2u) % 3u) * HU);
-            }
+        const unsigned long long k = (((unsigned long long)__builtin_amdgcn_readfirstlane(ctl[1]) << 32) |
+                                      __builtin_amdgcn_readfirstlane(ctl[0])) + step_off;
+        kk = (uint32_t)k;
+        const rsrc_t gbits = make_rsrc((k & 1) ? a.iota1 : a.iota0, ((total + 511u) >> 9) << 6);
+        if (H.on) {
+            const uint32_t HU = a.hub_units;
+            const uint32_t k2 = kk & 1u;
+            // k mod 3 (2^32 = 1 mod 3)
+            const uint32_t k3 = ((uint32_t)(k >> 32) % 3u + kk % 3u) % 3u;
+            H.t_prev = in_vgpr((k2 ^ 1u) * HU);
+            H.t_cur = in_vgpr(k2 * HU);
+            H.d_cur = in_vgpr((2u + k3) * HU);
+            H.d_next = in_vgpr((2u + (k3 + 1u) % 3u) * HU);
+            H.d_clr = in_vgpr((2u + (k3 + 2u) % 3u) * HU);
         }
         load_table();
 
@@ -365,6 +385,7 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
                     const uint32_t h = hub ? u0 + l - H.base : 0u;
                     ht[i] = ld32(H.tr, hub ? (H.t_prev + h) << 2 : OOB);
                     hd[i] = ld32(H.tr, hub ? (H.d_cur + h) << 2 : OOB);
+                    if (LGW < 4) ht[i] += hd[i]; // (one register each)
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -384,7 +405,7 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
                     const bool hub = l < nvalid && u0 + l >= H.base;
                     if (__ballot(hub) != 0ull) {
                         const uint32_t h = hub ? u0 + l - H.base : 0u;
-                        const uint32_t pp = ht[i] + hd[i];
+                        const uint32_t pp = LGW < 4 ? ht[i] : ht[i] + hd[i];
                         st32(H.tr, hub ? (H.t_cur + h) << 2 : OOB, pp);
                         st32(H.tr, hub ? (H.d_clr + h) << 2 : OOB, 0u);
                         if (hub) p = (float)pp;
@@ -429,23 +450,28 @@ __device__ __forceinline__ void reps_body(const StepArgs& a, RepsShared<LGW>& S,
         // the next infectivity words of the group's chunks
         if (lane < W) {
             const uint32_t f0 = S.flip[wave][2 * lane], f1 = S.flip[wave][2 * lane + 1];
-            S.flip[wave][2 * lane] = 0u;
-            S.flip[wave][2 * lane + 1] = 0u;
+            // (a zero made here: one held through the walk is spilled to scratch
+            // memory, and a kernel with scratch starts later)
+            const uint32_t zero = in_vgpr(0u);
+            S.flip[wave][2 * lane] = zero;
+            S.flip[wave][2 * lane + 1] = zero;
             const uint32_t c = (g << LGW) + lane;
-            if (c < nchunks) ((uint2*)bits_out)[c] = make_uint2(w_lo ^ f0, w_hi ^ f1);
+            const auto& f = *fresh_args<LGW>(args);
+            if (c < nchunks) ((uint2*)((kk & 1u) ? f.iota0 : f.iota1))[c] = make_uint2(w_lo ^ f0, w_hi ^ f1);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 
-    if (H.on && H.n > 0) flush_pushes(a, H, lane0);
+    const auto& b = *fresh_args<LGW>(args);
+    if (H.on && H.n > 0) flush_pushes(b, H, fresh_lane());
 
     // this workgroup's transitions; the reduce kernel turns their sums into
     // counts (the counts before the step, plus and minus the transitions)
     __syncthreads();
-    uint32_t* out = a.part + ((size_t)a.step_off * nblocks + block) * (4 * R);
-    for (uint32_t i = tid; i < 4 * R; i += REPS_TPB) out[i] = S.cnt[i];
+    uint32_t* out = b.part + ((size_t)step_off * nblocks + block) * (4 * R);
+    for (uint32_t i = wave * 64u + fresh_lane(); i < 4 * R; i += REPS_TPB) out[i] = S.cnt[i];
 }
 
 } // namespace fsk

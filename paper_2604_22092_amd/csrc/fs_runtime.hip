@@ -516,9 +516,11 @@ bool layout_cached(fs_graph* g, int32_t R, int32_t heavy_deg, int32_t seg_edges,
 //  summary screens most edges (regular d = 10, N = 1e6: 37 / 55; on a
 //  Barabasi-Albert graph, which streams, 101 / 51).
 //  The widest group shares most work, the narrowest gives small sims more
-//  wavefronts: the widest that leaves REPS_GROUPS of them (Barabasi-Albert 4, N =
-//  3e5, R = 16: 4688 groups of 16 chunks 33.3 us, 9375 of 8 34.0, 18750 of 4
-//  38; Erdos-Renyi 10, N = 3e4, R = 64: 1875 / 3750 / 7500 groups 14.0 / 12.8 / 17).
+//  wavefronts: the widest that leaves REPS_GROUPS of them, REPS_GROUPS16 of 16
+//  chunks (us per step: Barabasi-Albert 4, N = 3e5, R = 16: 4688 groups of 16
+//  33.3, 9375 of 8 34.0, 18750 of 4 38; regular d = 10, N = 2e5, R = 16 compact:
+//  3125 of 16 21.4, 6250 of 8 20.9; Erdos-Renyi 10, N = 1e5, R = 16: 3125 of 8
+//  14.1, 6250 of 4 15.6; N = 3e4, R = 64: 1875 of 16 14.0, 3750 of 8 12.5).
 int replica_width(const fs_graph* g, const fs_sim_params& p, int lgR, int32_t limit)
 {
     if (lgR < 2 || g->d_weights || p.shedding != FS_SHED_CONSTANT || p.adaptive || p.record_rates || p.compaction)
@@ -528,7 +530,7 @@ int replica_width(const fs_graph* g, const fs_sim_params& p, int lgR, int32_t li
     const bool uniform = g->min_degree == g->max_degree && g->max_degree <= fsi::UNIFORM_MAX_DEG;
     if (chunks < fsi::REPS_CHUNKS || (uniform && lgR < 3)) return -1;
     int w = std::min(lgR, 4);
-    while (w > 2 && (chunks >> w) < fsi::REPS_GROUPS) --w;
+    while (w > 2 && (chunks >> w) < (w == 4 ? fsi::REPS_GROUPS16 : fsi::REPS_GROUPS)) --w;
     return w;
 }
 

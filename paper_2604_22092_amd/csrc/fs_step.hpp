@@ -320,7 +320,8 @@ struct HubCtx {
 // occurrence.  The lists of up to 64 queued units are flattened over the
 // wavefront: lane l takes list entry f = f0 + l, finds its unit by a binary
 // search of the lists' prefix sums, and adds to the row it names.
-__device__ __forceinline__ void flush_pushes(const StepArgs& a, HubCtx& H, uint32_t lane)
+template <class Args>
+__device__ __forceinline__ void flush_pushes(const Args& a, HubCtx& H, uint32_t lane)
 {
     // (the queue was written by other lanes of this wavefront)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
