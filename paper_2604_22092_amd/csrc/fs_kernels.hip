@@ -6,11 +6,12 @@
 //   pressure gather over the incoming CSR row (S units only: the rate of
 //   E, I and R units does not depend on it), rate by state, Philox draw,
 //   state/age advance in place, next-step infectivity into the other
-//   ping-pong buffer, and exact per-step S/E/I/R counts.
+//   ping-pong buffer, and the step's exact transitions.
 // A sequence of r step launches (launch j runs step ctl->step + j) is
-// followed by one reduce launch that sums the per-workgroup count partials of
-// every step into the count history, and one single-thread launch that
-// advances ctl->step by r.  No step kernel uses a global atomic.
+// followed by one reduce launch that sums the workgroups' transitions of every
+// step, writes the counts after each step to the history and advances
+// ctl->step by r.  No step kernel uses a global atomic across workgroups but the
+// pushes of binned rows.
 #include <hip/hip_runtime.h>
 
 #include "fs_device.hpp"
@@ -154,34 +155,57 @@ __global__ __launch_bounds__(WG) void summary_kernel(SumArgs q)
 // Pushed pressure of the binned rows recounted from a bitmap (after a change
 // of states from the host): out[h] for hub unit h = (row - hub_base) * R + r
 // is the number of infectious in-neighbours of the row in replica r, counted
-// with multiplicity.  One wavefront per row: lane l takes edge offset l / R
-// and replica l % R, and each edge pass's bits are counted per replica by a
-// ballot, as the heavy-row kernels count integer partials.
+// with multiplicity.  Lane l takes edge offset l / R and replica l % R, and each
+// edge pass's bits are counted per replica by a ballot, as the heavy-row kernels
+// count integer partials.  What bounds it is the largest row's chain of column
+// and bitmap loads: the loads of RU passes are issued together, and `team`
+// wavefronts of a workgroup share a row (Barabasi-Albert 4, N = 3e5, R = 16, one
+// wavefront and one pass at a time 124 us, now 29; 5, N = 1e6, R = 1
+// 51 us, now 38).
+constexpr int RU = 8;
 __global__ __launch_bounds__(WG) void hub_recount_kernel(const int32_t* __restrict__ row_ptr,
                                                          const int32_t* __restrict__ col_ind, int32_t hub_base,
-                                                         uint32_t hubs, int32_t lgR,
+                                                         uint32_t hubs, int32_t lgR, uint32_t team,
                                                          const uint32_t* __restrict__ bits,
                                                          uint32_t* __restrict__ out)
 {
+    __shared__ uint32_t part[WG / 64][64];
     const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t R = 1u << lgR;
     const uint32_t per = 64u >> lgR;
-    const uint32_t eoff = lane >> lgR;
     const uint32_t rep = lane & (R - 1);
     unsigned long long rmask = 1ull; // lanes of replica 0: every R-th lane
     for (uint32_t sh = R; sh < 64u; sh <<= 1) rmask |= rmask << sh;
-    const uint32_t nw = gridDim.x * (WG / 64);
-    for (uint32_t h = blockIdx.x * (WG / 64) + (threadIdx.x >> 6); h < hubs; h += nw) {
-        const int32_t row = hub_base + (int32_t)h;
-        const int32_t e1 = row_ptr[row + 1];
+    const uint32_t rows = WG / 64 / team; // rows of a workgroup at a time
+    for (uint32_t h0 = blockIdx.x * rows; h0 < hubs; h0 += gridDim.x * rows) {
+        const uint32_t h = h0 + wave / team;
         uint32_t c = 0;
-        for (int32_t e = row_ptr[row] + (int32_t)eoff;; e += (int32_t)per) {
-            const bool in = e < e1;
-            if (__ballot(in) == 0ull) break;
-            const uint32_t b = in ? bit_at(bits, ((uint32_t)col_ind[e] << lgR) + rep) : 0u;
-            c += (uint32_t)__popcll(__ballot(b != 0u) & (rmask << rep));
+        if (h < hubs) {
+            const int32_t row = hub_base + (int32_t)h;
+            const uint32_t e1 = (uint32_t)row_ptr[row + 1];
+            for (uint32_t e0 = (uint32_t)row_ptr[row] + wave % team * (RU * per); e0 < e1; e0 += team * (RU * per)) {
+                int32_t col[RU];
+                uint32_t b[RU];
+#pragma unroll
+                for (int u = 0; u < RU; ++u) {
+                    const uint32_t e = e0 + (uint32_t)u * per + (lane >> lgR);
+                    col[u] = e < e1 ? col_ind[e] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < RU; ++u) b[u] = col[u] >= 0 ? bit_at(bits, ((uint32_t)col[u] << lgR) + rep) : 0u;
+#pragma unroll
+                for (int u = 0; u < RU; ++u) c += (uint32_t)__popcll(__ballot(b[u] != 0u) & (rmask << rep));
+            }
         }
-        if (lane < R) out[(size_t)h * R + lane] = c;
+        if (team > 1) {
+            part[wave][lane] = c;
+            __syncthreads();
+            c = 0;
+            for (uint32_t w = 0; w < team; ++w) c += part[wave / team * team + w][lane];
+            __syncthreads();
+        }
+        if (h < hubs && wave % team == 0 && lane < R) out[(size_t)h * R + lane] = c;
     }
 }
 
@@ -452,9 +476,11 @@ hipError_t launch_hub_recount(const int32_t* row_ptr, const int32_t* col_ind, in
                               int32_t lgR, const uint32_t* bits, uint32_t* out, hipStream_t s)
 {
     if (hubs == 0) return hipSuccess;
-    unsigned g = grid_for((size_t)hubs, WG / 64);
+    // few binned rows are long ones: a workgroup each; many, a wavefront each
+    const uint32_t team = hubs <= 8192u ? WG / 64 : 1u;
+    unsigned g = grid_for((size_t)hubs, WG / 64 / team);
     if (g > 8192) g = 8192;
-    hipLaunchKernelGGL(hub_recount_kernel, dim3(g), dim3(WG), 0, s, row_ptr, col_ind, hub_base, hubs, lgR, bits,
+    hipLaunchKernelGGL(hub_recount_kernel, dim3(g), dim3(WG), 0, s, row_ptr, col_ind, hub_base, hubs, lgR, team, bits,
                        out);
     return hipGetLastError();
 }
