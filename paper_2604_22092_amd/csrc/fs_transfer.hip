@@ -89,7 +89,9 @@ void give(Slot& s)
 
 // Runs f(first node, nodes, slot) for every piece of n nodes, on as many
 // threads as there are pieces (up to MAX_THREADS), each with a pinned buffer of
-// its own on `device`.  f returns a HIP error, which ends the run.
+// its own on `device`.  f returns a HIP error, which ends the run.  The handle
+// hipStreamPerThread names another stream on every thread, so there the
+// caller's thread, which has queued what the pieces wait for, takes them all.
 template <class F>
 fs_status for_pieces(int device, hipStream_t stream, size_t n, F f)
 {
@@ -110,7 +112,8 @@ fs_status for_pieces(int device, hipStream_t stream, size_t n, F f)
         if (e != hipSuccess) err.compare_exchange_strong(ok, (int)e);
     };
     std::vector<std::thread> threads;
-    const size_t extra = std::min(pieces, MAX_THREADS) - (pieces ? 1 : 0);
+    const size_t most = stream == hipStreamPerThread ? 1 : MAX_THREADS;
+    const size_t extra = std::min(pieces, most) - (pieces ? 1 : 0);
     try {
         threads.reserve(extra);
         for (size_t i = 0; i < extra; ++i)
