@@ -340,14 +340,20 @@ __global__ __launch_bounds__(MTPB) void mk_rates_kernel(MkArgs a)
             return;
         }
     }
-    const bool control = a.force_control || ev > a.inertial_max || skip != 0u;
+    const bool all = a.model == FS_MARKOV_SIS;
+    // (pushes left out by a workgroup, in a step of few events: the recount
+    // stands for them and touches the nodes they would have)
+    const bool recount = a.force_control || ev > a.inertial_max;
+    const bool control = recount || skip != 0u;
     uint32_t A = 0, M = 0, nE = 0, nI = 0, nS = 0;
     if (control) {
         for (uint32_t v = base + tid; v < end; v += tpb) {
             const int x = (int)a.state[v];
             int c = 0;
-            for (int32_t e = a.row_ptr[v]; e < a.row_ptr[v + 1]; ++e) c += a.state[a.col_ind[e]] == ST_I;
-            a.infl[v] = c;
+            if (recount || all || x == ST_S) {
+                for (int32_t e = a.row_ptr[v]; e < a.row_ptr[v + 1]; ++e) c += a.state[a.col_ind[e]] == ST_I;
+                a.infl[v] = c;
+            }
             a.pending[v] = 0;
             if (x == ST_S) {
                 A += (uint32_t)c;
@@ -369,7 +375,8 @@ __global__ __launch_bounds__(MTPB) void mk_rates_kernel(MkArgs a)
                 }
             }
             if ((d.x | d.y | d.z | d.w) != 0) {
-                f = make_int4(f.x + d.x, f.y + d.y, f.z + d.z, f.w + d.w);
+                auto add = [&](int v, int c, uint32_t j) { return all || ((w >> (8u * j)) & 7u) == (uint32_t)ST_S ? v + c : v; };
+                f = make_int4(add(f.x, d.x, 0), add(f.y, d.y, 1), add(f.z, d.z, 2), add(f.w, d.w, 3));
                 *(int4*)(a.infl + i) = f;
                 *(int4*)(a.pending + i) = make_int4(0, 0, 0, 0);
             }
