@@ -15,11 +15,13 @@
 //          other workgroups still read the influences of this step.  Without
 //          I -> S (SEIR, SIR) only susceptible targets are updated: no other
 //          node reads its influence again;
-//   rates  (dense): adds the pending changes to the influences, or (Control
-//          Mode: many events in the step) recounts every influence from the
-//          incoming CSR, and writes per-workgroup partials (sum of S
-//          influences, max S influence, #E, #I) and counts; after a step
-//          without transitions it keeps the old ones.
+//   rates  (dense): adds the pending changes to the influences (without I -> S
+//          only to nodes still susceptible: one that leaves S in this step was
+//          pushed to or not by who came first, and keeps the influence it left
+//          with), or (Control Mode: many events in the step) recounts every
+//          influence from the incoming CSR, and writes per-workgroup partials
+//          (sum of S influences, max S influence, #E, #I) and counts; after a
+//          step without transitions it keeps the old ones.
 // Both modes give the same integer influences on every node that can still
 // read them (every susceptible node; every node under SIS), so results do not
 // depend on which ran.  Per-step counts, tau and event totals go to rings on the
