@@ -253,10 +253,7 @@ fs_status batch_sequence(fs_batch* b, uint32_t r)
     const uint32_t M = (uint32_t)b->members.size();
     // the instantiation with rate recording only when a member records them
     bool rates = false;
-    for (fs_sim* s : b->members) {
-        rates = rates || s->d_rates != nullptr;
-        FS_HIP(refresh_base(s));
-    }
+    for (const fs_sim* s : b->members) rates = rates || s->d_rates != nullptr;
     const void* kfn[4] = {fsk::step_batch_kernel_fn(b->storage, b->weighted == 1, rates),
                           fsk::reps_kernel_fn(b->storage, 2, true), fsk::reps_kernel_fn(b->storage, 3, true),
                           fsk::reps_kernel_fn(b->storage, 4, true)};

@@ -234,43 +234,29 @@ __global__ __launch_bounds__(WG) void recount_kernel(const void* state_v, int32_
     }
 }
 
-// Exact counts of every replica added into base[R][4] (zeroed before): the
-// counts the steps' transitions are added to.
-template <int STORAGE>
-__global__ __launch_bounds__(WG) void count_all_kernel(const void* state_v, uint32_t total, int32_t lgR, uint32_t* base)
+// The counts the steps' transitions are added to, [replica][compartment],
+// cleared by one workgroup of the kernel that changes the states and counted
+// anew by the next one (rebuild_bits_kernel).
+__device__ __forceinline__ void clear_base(uint32_t* base, int32_t lgR)
 {
-    using state_t = typename Store<STORAGE>::state_t;
-    const state_t* state = (const state_t*)state_v;
-    __shared__ uint32_t s[4 * 64];
-    const uint32_t C = 4u << lgR, rm = (1u << lgR) - 1u;
-    for (uint32_t i = threadIdx.x; i < C; i += WG) s[i] = 0;
-    __syncthreads();
-    if (lgR == 0) {
-        uint32_t c[4] = {0u, 0u, 0u, 0u};
-        for (uint32_t u0 = blockIdx.x * WG; u0 < total; u0 += gridDim.x * WG) {
-            const uint32_t u = u0 + threadIdx.x;
-            const int x = u < total ? (int)state[u] : -1;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) c[q] += (uint32_t)__popcll(__ballot(x == q));
-        }
-        if ((threadIdx.x & 63u) == 0u)
-            for (int q = 0; q < 4; ++q) atomicAdd(&s[q], c[q]); // LDS
-    } else {
-        for (uint32_t u = blockIdx.x * WG + threadIdx.x; u < total; u += gridDim.x * WG)
-            atomicAdd(&s[(u & rm) * 4u + (uint32_t)state[u]], 1u); // LDS
-    }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < C; i += WG)
-        if (s[i]) atomicAdd(&base[i], s[i]);
+    if (blockIdx.x == 0)
+        for (uint32_t i = threadIdx.x; i < 4u << lgR; i += blockDim.x) base[i] = 0u;
+}
+
+// Those of a new sim: every node in S.
+__global__ void init_base_kernel(uint32_t* base, uint32_t n)
+{
+    base[threadIdx.x] = (threadIdx.x & 3u) == 0u ? n : 0u;
 }
 
 // Writes one replica's contiguous states and ages (caller's node order) into
 // the interleaved internal layout.
 template <int STORAGE>
 __global__ void put_replica_kernel(void* state_v, void* age_v, const uint8_t* src_state, const void* src_age,
-                                   const int32_t* orig, int32_t n, int32_t lgR, int32_t replica)
+                                   const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, uint32_t* base)
 {
     using S = Store<STORAGE>;
+    clear_base(base, lgR);
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (uint32_t)n) return;
     const size_t u = ((size_t)i << lgR) + replica;
@@ -279,18 +265,59 @@ __global__ void put_replica_kernel(void* state_v, void* age_v, const uint8_t* sr
     ((typename S::age_t*)age_v)[u] = ((const typename S::age_t*)src_age)[c];
 }
 
-// Rebuilds an infectivity bitmap from the states: one 64-bit word per wave.
-template <int STORAGE>
-__global__ __launch_bounds__(WG) void rebuild_bits_kernel(const void* state_v, uint32_t total,
-                                                          unsigned long long* bits, uint32_t words)
+// Rebuilds an infectivity bitmap from the states and (COUNT) adds the exact
+// counts of every replica to base[R][4]: each wavefront takes RB_UN chunks of 64
+// units at a time, their loads issued together.  The counts belong to the
+// change of the states, not to the steps after it: a step sequence captured by
+// the caller then starts from the counts of whatever was loaded before its
+// replay.  Few, large workgroups, since each adds to the same few counters (N =
+// 1e6: 489 of 256 threads 8.1 us, 123 of 1024 5.1; the bitmap alone and a clear
+// and a count of their own in front of the steps 4.0 + 1.4 + 8.5; N = 3e7 52 + 45 in
+// two passes, 36 in one).
+constexpr uint32_t RB_UN = 8, RB_TPB = 1024;
+template <int STORAGE, bool COUNT>
+__global__ __launch_bounds__(RB_TPB) void rebuild_bits_kernel(const void* state_v, uint32_t total, int32_t lgR,
+                                                          unsigned long long* bits, uint32_t words, uint32_t* base)
 {
     using state_t = typename Store<STORAGE>::state_t;
-    const uint32_t unit = blockIdx.x * WG + threadIdx.x;
-    const bool valid = unit < total;
-    const int x = valid ? (int)((const state_t*)state_v)[unit] : -1;
-    const unsigned long long m = __ballot(x == ST_I);
-    const uint32_t w = unit >> 6;
-    if ((threadIdx.x & 63) == 0 && w < words) bits[w] = m;
+    const state_t* state = (const state_t*)state_v;
+    __shared__ uint32_t s[4 * 64];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t C = 4u << lgR, R = 1u << lgR;
+    if (COUNT) {
+        if (threadIdx.x < C) s[threadIdx.x] = 0u;
+        __syncthreads();
+    }
+    unsigned long long rmask = 1ull; // lanes of this lane's replica: every R-th
+    for (uint32_t sh = R; sh < 64u; sh <<= 1) rmask |= rmask << sh;
+    rmask <<= lane & (R - 1u);
+    uint32_t c[4] = {0u, 0u, 0u, 0u};
+    const uint32_t stride = gridDim.x * (RB_TPB / 64) * RB_UN;
+    for (uint32_t w0 = (blockIdx.x * (RB_TPB / 64) + (threadIdx.x >> 6)) * RB_UN; w0 < words; w0 += stride) {
+        int x[RB_UN];
+#pragma unroll
+        for (uint32_t u = 0; u < RB_UN; ++u) {
+            const uint32_t unit = (w0 + u) * 64u + lane;
+            x[u] = unit < total ? (int)state[unit] : -1;
+        }
+        unsigned long long word = 0ull; // lane u holds word w0 + u
+#pragma unroll
+        for (uint32_t u = 0; u < RB_UN; ++u) {
+            const unsigned long long m = __ballot(x[u] == ST_I);
+            word = lane == u ? m : word;
+            if (COUNT) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[q] += (uint32_t)__popcll((q == ST_I ? m : __ballot(x[u] == q)) & rmask);
+            }
+        }
+        if (lane < RB_UN && w0 + lane < words) bits[w0 + lane] = word;
+    }
+    if (COUNT) {
+        if (lane < R)
+            for (int q = 0; q < 4; ++q) atomicAdd(&s[lane * 4u + (uint32_t)q], c[q]); // LDS
+        __syncthreads();
+        if (threadIdx.x < C && s[threadIdx.x] != 0u) atomicAdd(&base[threadIdx.x], s[threadIdx.x]);
+    }
 }
 
 template <int STORAGE>
@@ -317,10 +344,11 @@ __global__ void get_rates_kernel(const float* rates, float* dst, const int32_t* 
 // Seeds listed nodes of one replica (or all replicas) into `comp` at age 0.
 template <int STORAGE>
 __global__ void seed_kernel(void* state_v, void* age_v, const int64_t* nodes, int64_t count, int32_t lgR,
-                            int32_t replica, int32_t comp)
+                            int32_t replica, int32_t comp, uint32_t* base)
 {
     using S = Store<STORAGE>;
     const uint32_t R = 1u << lgR;
+    clear_base(base, lgR);
     const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= (uint64_t)count * (replica < 0 ? R : 1u)) return;
     const uint64_t idx = replica < 0 ? j / R : j;
@@ -528,29 +556,32 @@ const void* heavy_batch_kernel_fn(bool weighted)
 const void* reduce_batch_kernel_fn() { return (const void*)&reduce_batch_kernel; }
 
 hipError_t launch_put_replica(int storage, void* state, void* age, const uint8_t* src_state, const void* src_age,
-                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, hipStream_t s)
+                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, uint32_t* base,
+                              hipStream_t s)
 {
     if (n == 0) return hipSuccess;
     unsigned g = grid_for((size_t)n, 256);
     if (storage == 0)
         hipLaunchKernelGGL(put_replica_kernel<0>, dim3(g), dim3(256), 0, s, state, age, src_state, src_age, orig, n,
-                           lgR, replica);
+                           lgR, replica, base);
     else
         hipLaunchKernelGGL(put_replica_kernel<1>, dim3(g), dim3(256), 0, s, state, age, src_state, src_age, orig, n,
-                           lgR, replica);
+                           lgR, replica, base);
     return hipGetLastError();
 }
 
-hipError_t launch_rebuild_bits(int storage, const void* state, uint32_t total, unsigned long long* bits,
-                               uint32_t words, hipStream_t s)
+hipError_t launch_rebuild_bits(int storage, const void* state, uint32_t total, int32_t lgR, unsigned long long* bits,
+                               uint32_t words, uint32_t* base, hipStream_t s)
 {
-    unsigned g = grid_for((size_t)words * 64, WG);
-    if (g == 0) return hipSuccess;
-    if (storage == 0)
-        hipLaunchKernelGGL(rebuild_bits_kernel<0>, dim3(g), dim3(WG), 0, s, state, total, bits, words);
-    else
-        hipLaunchKernelGGL(rebuild_bits_kernel<1>, dim3(g), dim3(WG), 0, s, state, total, bits, words);
-    return hipGetLastError();
+    // (bounded, so that few workgroups add to the same few counters)
+    const uint32_t per = RB_TPB / 64 * RB_UN;
+    const unsigned g = std::max(1u, std::min((words + per - 1u) / per, lgR >= 3 ? 128u : 256u));
+    auto go = [&](auto* fn) {
+        hipLaunchKernelGGL(fn, dim3(g), dim3(RB_TPB), 0, s, state, total, lgR, bits, words, base);
+        return hipGetLastError();
+    };
+    if (base) return storage == 0 ? go(rebuild_bits_kernel<0, true>) : go(rebuild_bits_kernel<1, true>);
+    return storage == 0 ? go(rebuild_bits_kernel<0, false>) : go(rebuild_bits_kernel<1, false>);
 }
 
 hipError_t launch_get_replica(int storage, const void* state, const void* age, uint8_t* dst_state, void* dst_age,
@@ -577,15 +608,15 @@ hipError_t launch_get_rates(const float* rates, float* dst, const int32_t* orig,
 }
 
 hipError_t launch_seed(int storage, void* state, void* age, const int64_t* nodes, int64_t count, int32_t lgR,
-                       int32_t replica, int32_t comp, hipStream_t s)
+                       int32_t replica, int32_t comp, uint32_t* base, hipStream_t s)
 {
     const size_t work = (size_t)count * (replica < 0 ? (1u << lgR) : 1u);
     if (work == 0) return hipSuccess;
     unsigned g = grid_for(work, 256);
     if (storage == 0)
-        hipLaunchKernelGGL(seed_kernel<0>, dim3(g), dim3(256), 0, s, state, age, nodes, count, lgR, replica, comp);
+        hipLaunchKernelGGL(seed_kernel<0>, dim3(g), dim3(256), 0, s, state, age, nodes, count, lgR, replica, comp, base);
     else
-        hipLaunchKernelGGL(seed_kernel<1>, dim3(g), dim3(256), 0, s, state, age, nodes, count, lgR, replica, comp);
+        hipLaunchKernelGGL(seed_kernel<1>, dim3(g), dim3(256), 0, s, state, age, nodes, count, lgR, replica, comp, base);
     return hipGetLastError();
 }
 
@@ -598,15 +629,9 @@ hipError_t launch_clear_u32(uint32_t* p, size_t n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_count_all(int storage, const void* state, uint32_t total, int32_t lgR, uint32_t* base, hipStream_t s)
+hipError_t launch_init_base(uint32_t* base, uint32_t n, int32_t lgR, hipStream_t s)
 {
-    hipError_t e = launch_clear_u32(base, (size_t)4 << lgR, s);
-    if (e != hipSuccess) return e;
-    const uint32_t g = std::max(1u, std::min((total + WG * 16u - 1u) / (WG * 16u), 1024u));
-    if (storage == 0)
-        hipLaunchKernelGGL(count_all_kernel<0>, dim3(g), dim3(WG), 0, s, state, total, lgR, base);
-    else
-        hipLaunchKernelGGL(count_all_kernel<1>, dim3(g), dim3(WG), 0, s, state, total, lgR, base);
+    hipLaunchKernelGGL(init_base_kernel, dim3(1), dim3(4u << lgR), 0, s, base, n);
     return hipGetLastError();
 }
 

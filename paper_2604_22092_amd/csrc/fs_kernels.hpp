@@ -76,26 +76,28 @@ const void* heavy_batch_kernel_fn(bool weighted);
 const void* reduce_batch_kernel_fn();
 // One replica's states (bytes) and ages between the caller's node order and
 // the interleaved internal layout; orig: internal -> caller's id, nullptr for
-// the identity.
+// the identity.  The kernels that change states clear base (the counts [R][4]
+// before the next step), and launch_rebuild_bits with the same base, which has
+// to follow, counts it anew (nullptr: the bitmap only).
 hipError_t launch_put_replica(int storage, void* state, void* age, const uint8_t* src_state, const void* src_age,
-                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, hipStream_t s);
-hipError_t launch_rebuild_bits(int storage, const void* state, uint32_t total, unsigned long long* bits,
-                               uint32_t words, hipStream_t s);
+                              const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, uint32_t* base,
+                              hipStream_t s);
+hipError_t launch_rebuild_bits(int storage, const void* state, uint32_t total, int32_t lgR, unsigned long long* bits,
+                               uint32_t words, uint32_t* base, hipStream_t s);
 hipError_t launch_get_replica(int storage, const void* state, const void* age, uint8_t* dst_state, void* dst_age,
                               const int32_t* orig, int32_t n, int32_t lgR, int32_t replica, hipStream_t s);
 hipError_t launch_get_rates(const float* rates, float* dst, const int32_t* orig, int32_t n, int32_t lgR,
                             int32_t replica, hipStream_t s);
 hipError_t launch_seed(int storage, void* state, void* age, const int64_t* nodes, int64_t count, int32_t lgR,
-                       int32_t replica, int32_t comp, hipStream_t s);
+                       int32_t replica, int32_t comp, uint32_t* base, hipStream_t s);
 hipError_t launch_clear_u32(uint32_t* p, size_t n, hipStream_t s);
 // The replica step (reps_kernel(StepArgs), REPS_TPB = STREAM_TPB threads) with
 // groups of 2^lgW chunks, lgW in {2, 3, 4}, or its batched form
 // reps_batch_kernel(const StepArgs*, const uint32_t* first, uint32_t members,
 // uint32_t step_off); nullptr for another lgW.
 const void* reps_kernel_fn(int storage, int lgW, bool batch);
-// Counts of every replica of `total` units into base[R][4].
-hipError_t launch_count_all(int storage, const void* state, uint32_t total, int32_t lgR, uint32_t* base,
-                            hipStream_t s);
+// The base of a sim of n nodes, all in S.
+hipError_t launch_init_base(uint32_t* base, uint32_t n, int32_t lgR, hipStream_t s);
 hipError_t launch_set_ctl(fsi::Ctl* ctl, unsigned long long step, hipStream_t s);
 hipError_t launch_eval_hazard(const fsi::HazardDev& h, int32_t storage, const void* ages, float* out, int64_t n,
                               hipStream_t s);

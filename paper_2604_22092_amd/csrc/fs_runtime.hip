@@ -572,15 +572,6 @@ fs_status set_shape(fs_sim* s, int mode, int lgW)
     return FS_OK;
 }
 
-hipError_t refresh_base(fs_sim* s)
-{
-    if (!s->base_stale) return hipSuccess;
-    const hipError_t e = fsk::launch_count_all(s->storage, s->d_state, (uint32_t)s->g->n << s->lgR, s->lgR, s->d_base,
-                                               s->stream);
-    if (e == hipSuccess) s->base_stale = false;
-    return e;
-}
-
 // Whether a sim of these parameters may take packed columns: the
 // single-replica step of an unweighted graph (not age-dependent shedding
 // together with rate recording or compaction), unless the caller asks for
@@ -783,8 +774,9 @@ hipError_t refresh_derived(fs_sim* s, int64_t step)
     // compaction: a chunk the next refresh drops is never written again, so
     // the other bitmap must hold its (all-R, zero) words too
     if (s->d_live &&
-        (e = fsk::launch_rebuild_bits(s->storage, s->d_state, total, (unsigned long long*)s->d_iota[(step + 1) & 1],
-                                      s->bit_words, s->stream)) != hipSuccess)
+        (e = fsk::launch_rebuild_bits(s->storage, s->d_state, total, s->lgR,
+                                      (unsigned long long*)s->d_iota[(step + 1) & 1], s->bit_words, nullptr,
+                                      s->stream)) != hipSuccess)
         return e;
     if (s->d_shed[0] &&
         (e = fsk::launch_rebuild_shed(s->storage, s->d_state, s->d_age, total, s->shed, s->d_shed[step & 1],
@@ -898,7 +890,6 @@ fs_status build_graph_exec(fs_sim* s, int b)
 
 fs_status launch_sequence(fs_sim* s, uint32_t r)
 {
-    FS_HIP(refresh_base(s));
     SeqArgs q;
     make_seq(s, r, q);
     if (s->d_act) {
@@ -943,11 +934,10 @@ fs_status check_seed(const fs_sim* s, int32_t replica, int64_t count, const int6
 
 fs_status seed_staged(fs_sim* s, int32_t replica, const int64_t* d_nodes, int64_t count, int32_t compartment)
 {
-    s->base_stale = true;
-    FS_HIP(fsk::launch_seed(s->storage, s->d_state, s->d_age, d_nodes, count, s->lgR, replica, compartment,
+    FS_HIP(fsk::launch_seed(s->storage, s->d_state, s->d_age, d_nodes, count, s->lgR, replica, compartment, s->d_base,
                             s->stream));
-    FS_HIP(fsk::launch_rebuild_bits(s->storage, s->d_state, (uint32_t)(s->g->n * s->R),
-                                    (unsigned long long*)s->d_iota[s->step & 1], s->bit_words, s->stream));
+    FS_HIP(fsk::launch_rebuild_bits(s->storage, s->d_state, (uint32_t)(s->g->n * s->R), s->lgR,
+                                    (unsigned long long*)s->d_iota[s->step & 1], s->bit_words, s->d_base, s->stream));
     FS_HIP(refresh_derived(s, s->step));
     FS_HIP(refresh_summary(s));
     FS_HIP(hipStreamSynchronize(s->stream));
@@ -1093,6 +1083,7 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
                   {s->d_iota[1], (size_t)s->bit_words * 8, {}},
                   {s->d_ctl, sizeof(fsi::Ctl), {}},
                   {s->d_hist, (size_t)s->H * s->R * 4 * sizeof(uint32_t), {}},
+                  {s->d_base, (size_t)s->R * 4 * sizeof(uint32_t), {}},
                   {s->d_lam_part, 2 * (size_t)s->G * sizeof(float), {}},
                   {s->d_shed[0], (size_t)s->g->n * s->R * shed_bytes(s->storage), {}},
                   {s->d_shed[1], (size_t)s->g->n * s->R * shed_bytes(s->storage), {}},
@@ -1166,7 +1157,6 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
                 best_mode = m;
                 best = c;
             }
-            s->base_stale = true;
             for (auto& b : bufs)
                 if (b.live && hipMemcpyAsync(b.live, b.copy.p, b.bytes, hipMemcpyDeviceToDevice, s->stream) != hipSuccess) {
                     st = fail(FS_ERR_DEVICE, "restore");
@@ -1177,7 +1167,6 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    s->base_stale = true;
     for (auto& b : bufs)
         if (b.live) (void)hipMemcpyAsync(b.live, b.copy.p, b.bytes, hipMemcpyDeviceToDevice, s->stream);
     FS_HIP(hipStreamSynchronize(s->stream));
@@ -1515,6 +1504,7 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
         (e = hipMemsetAsync(s->d_iota[1], 0, (size_t)s->bit_words * 8, s->stream)) != hipSuccess ||
         (s->d_rates && (e = hipMemsetAsync(s->d_rates, 0, units * sizeof(float), s->stream)) != hipSuccess) ||
         (e = hipMemsetAsync(s->d_ctl, 0, sizeof(fsi::Ctl), s->stream)) != hipSuccess ||
+        (e = fsk::launch_init_base(s->d_base, (uint32_t)g->n, s->lgR, s->stream)) != hipSuccess ||
         (e = hipMemsetAsync(s->d_hist, 0, hist_words * sizeof(uint32_t), s->stream)) != hipSuccess ||
         (s->d_summary &&
          (e = hipMemsetAsync(s->d_summary, 0, ((size_t)s->sum_bits + 511) / 512 * 64, s->stream)) != hipSuccess) ||
@@ -1734,7 +1724,6 @@ fs_status fs_step(fs_sim* s, int64_t n_steps)
             fs_status st = build_graph_exec(s, b);
             if (st != FS_OK) return st;
         }
-        FS_HIP(refresh_base(s));
         for (int64_t r = 0; r < n_steps / b; ++r) FS_HIP(hipGraphLaunch(s->exec, s->stream));
         rem = n_steps % b;
     }
@@ -1878,11 +1867,10 @@ fs_status fs_set_state(fs_sim* s, int32_t replica, const int32_t* state, const f
     if (bad_state) return fail(FS_ERR_INVALID_ARG, "state values must lie in [0, 3]");
     if (bad_age) return fail(FS_ERR_INVALID_ARG, "ages must be finite and >= 0");
     if (st != FS_OK) return st;
-    s->base_stale = true;
     FS_HIP(fsk::launch_put_replica(s->storage, s->d_state, s->d_age, d_state, tmp.p, order_of(s->g), (int32_t)n, s->lgR,
-                                   replica, s->stream));
-    FS_HIP(fsk::launch_rebuild_bits(s->storage, s->d_state, (uint32_t)units,
-                                    (unsigned long long*)s->d_iota[new_step & 1], s->bit_words, s->stream));
+                                   replica, s->d_base, s->stream));
+    FS_HIP(fsk::launch_rebuild_bits(s->storage, s->d_state, (uint32_t)units, s->lgR,
+                                    (unsigned long long*)s->d_iota[new_step & 1], s->bit_words, s->d_base, s->stream));
     FS_HIP(refresh_derived(s, new_step));
     // the step index, and (adaptive steps) a restart of the step-size rule at the cap
     FS_HIP(fsk::launch_set_ctl(s->d_ctl, (unsigned long long)new_step, s->stream));

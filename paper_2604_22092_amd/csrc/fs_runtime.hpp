@@ -125,11 +125,9 @@ struct fs_sim {
     // replica step (fs_reps.hpp): groups of 2^lgW chunks, or -1: the sim runs
     // its variant's kernel
     int lgW = -1;
-    // the counts [R][4] the steps' transitions are added to; stale after a
-    // change of states from the host, and then recounted before the next
-    // launch sequence
+    // the counts [R][4] the steps' transitions are added to: every change of
+    // states from the host leaves them counted anew
     uint32_t* d_base = nullptr;
-    bool base_stale = true;
     int64_t step = 0;      // index of the next step (host mirror of ctl->step)
     int64_t hist_from = 0; // first step whose count row is recorded
     StepArgs args{};
@@ -211,9 +209,6 @@ uint32_t heavy_grid(const fs_sim* s);       // WG-thread heavy workgroups (batch
 uint32_t sim_heavy_grid(const fs_sim* s);   // the sim's own heavy launch
 uint32_t sim_heavy_block(const fs_sim* s);
 fsi::HeavyArgs heavy_args(const fs_sim* s);
-// The counts before the sim's next launch sequence, if stale (on the sim's
-// stream; every path that queues its steps calls this first).
-hipError_t refresh_base(fs_sim* s);
 // Device bytes a sim of this graph and these parameters holds (an estimate
 // used for admission by memory budget).
 size_t sim_footprint(fs_graph* g, const fs_sim_params* p);
