@@ -553,25 +553,6 @@ void step_shape(const fs_sim* s, int mode, int lgW, uint32_t* tpb, uint32_t* G)
     *G = (uint32_t)std::min<size_t>(tiles, stream ? fsi::max_step_grid(s->R) : s->cus);
 }
 
-// Gives the sim the launch shape of (mode, lgW).  Count partials are written
-// and reduced within one launch sequence: nothing of them outlives it.
-fs_status set_shape(fs_sim* s, int mode, int lgW)
-{
-    uint32_t tpb, G;
-    step_shape(s, mode, lgW, &tpb, &G);
-    if (G != s->G || !s->d_part) {
-        sim_free(s, s->d_part);
-        s->d_part = nullptr;
-        FS_HIP(sim_alloc(s, (void**)&s->d_part, (size_t)s->chunk * G * (size_t)s->R * 4 * sizeof(uint32_t)));
-    }
-    s->mode = mode;
-    s->lgW = lgW;
-    s->tpb = tpb;
-    s->G = G;
-    s->args.part = s->d_part;
-    return FS_OK;
-}
-
 // Whether a sim of these parameters may take packed columns: the
 // single-replica step of an unweighted graph (not age-dependent shedding
 // together with rate recording or compaction), unless the caller asks for
@@ -642,19 +623,39 @@ hipError_t refresh_hubs(fs_sim* s, int64_t step)
 
 hipError_t refresh_summary(fs_sim* s);
 
-// The step kernel of the sim's current configuration (nullptr: none).
-const void* step_fn(const fs_sim* s)
+// The step kernel of a configuration (nullptr: none).
+const void* step_fn(const fs_sim* s, int mode, int lgW, const Layout* L)
 {
-    if (s->lgW >= 0) return fsk::reps_kernel_fn(s->storage, s->lgW, false);
-    return fsk::step_kernel_fn(s->storage, s->g->d_weights != nullptr, s->mode, s->layout ? s->layout->udeg : -1,
-                               s->d_shed[0] != nullptr, s->d_rates != nullptr || s->d_act != nullptr, s->lgR,
-                               s->layout ? s->layout->pbits : 0);
+    if (lgW >= 0) return fsk::reps_kernel_fn(s->storage, lgW, false);
+    return fsk::step_kernel_fn(s->storage, s->g->d_weights != nullptr, mode, L->udeg, s->d_shed[0] != nullptr,
+                               s->d_rates != nullptr || s->d_act != nullptr, s->lgR, L->pbits);
 }
 
-// Points sim s at the layout of its graph for (R, heavy_deg, seg_edges),
-// building it on first use, and gives s its own heavy-segment partials.
-// Cached layouts no sim uses any more, other than this one, are released.
-fs_status apply_bins(fs_sim* s, int32_t heavy_deg, int32_t seg_edges)
+// A sim's buffer until the sim takes it.
+struct SimBuf {
+    fs_sim* s;
+    void* p = nullptr;
+    explicit SimBuf(fs_sim* sim) : s(sim) {}
+    SimBuf(const SimBuf&) = delete;
+    ~SimBuf() { sim_free(s, p); }
+    // puts the new buffer in place of `old`, which is released
+    template <class T>
+    void into(T*& old)
+    {
+        sim_free(s, old);
+        old = (T*)p;
+        p = nullptr;
+    }
+};
+
+// Gives sim s the step variant `mode` and the layout of its graph for (R,
+// heavy_deg, seg_edges), built on first use: workgroup shape and count,
+// kernels, count partials, summary buffer and the binned rows' own buffers.
+// All that can fail comes before the first change, so a sim that a call leaves
+// with an error still steps as it did.  Count partials are written and reduced
+// within one launch sequence: nothing of them outlives it.  Cached layouts no
+// sim uses any more, other than this one, are released.
+fs_status configure(fs_sim* s, int mode, int32_t heavy_deg, int32_t seg_edges)
 {
     fs_graph* g = s->g;
     if (seg_edges < 64 || seg_edges > (1 << 20)) return fail(FS_ERR_INVALID_ARG, "segment_edges must be in [64, 2^20]");
@@ -674,17 +675,68 @@ fs_status apply_bins(fs_sim* s, int32_t heavy_deg, int32_t seg_edges)
             g->layouts[key] = L;
         }
     }
+    const bool weighted = g->d_weights != nullptr, shed = s->d_shed[0] != nullptr;
+    const void* kfn = step_fn(s, mode, lgW, L.get());
+    const void* hfn = fsk::heavy_kernel_fn(weighted, shed, mode == fsi::MODE_RESIDENT);
+    if (!kfn || !hfn) return fail(FS_ERR_DEVICE, "no step kernel for this configuration");
+    uint32_t tpb, G;
+    step_shape(s, mode, lgW, &tpb, &G);
+    // binned rows of an unweighted graph with constant shedding take pushed
+    // pressure; the others read segment partials
+    const bool hub_push = L->hubs > 0 && !shed;
+    const size_t HU = (size_t)L->hubs * (size_t)s->R;
+    const bool new_part = G != s->G || !s->d_part, new_layout = L != s->layout;
+    const bool new_summary = mode == fsi::MODE_SUMMARY && !s->d_summary;
+    SimBuf part(s), seg(s), hub(s), summary(s);
+    if (new_part) FS_HIP(sim_alloc(s, &part.p, (size_t)s->chunk * G * (size_t)s->R * 4 * sizeof(uint32_t)));
+    if (new_layout && L->nseg && !hub_push)
+        FS_HIP(sim_alloc(s, &seg.p, (size_t)L->nseg * (size_t)s->R * sizeof(uint32_t)));
+    if (new_layout && hub_push) FS_HIP(sim_alloc(s, &hub.p, 5 * HU * sizeof(uint32_t)));
+    if (new_summary) FS_HIP(sim_alloc(s, &summary.p, ((size_t)s->sum_bits + 511) / 512 * 64));
+
     drop_graph_exec(s);
     const bool left_replica_step = s->lgW >= 0 && lgW < 0;
-    fs_status shst = set_shape(s, s->mode, lgW);
-    if (shst != FS_OK) return shst;
-    sim_free(s, s->d_seg_part);
-    s->d_seg_part = nullptr;
-    sim_free(s, s->d_hub);
-    s->d_hub = nullptr;
-    s->hub_push = false;
-    s->args.hub_T = s->args.hub_D = nullptr;
+    const bool other_mode = mode != s->mode;
+    if (new_part) part.into(s->d_part);
+    if (new_layout) {
+        seg.into(s->d_seg_part);
+        hub.into(s->d_hub);
+    }
+    if (new_summary) summary.into(s->d_summary);
+    s->mode = mode;
+    s->lgW = lgW;
+    s->tpb = tpb;
+    s->G = G;
+    s->kfn = kfn;
+    s->hfn = hfn;
     s->layout = L;
+    s->nseg = L->nseg;
+    s->d_segs = L->d_segs;
+    s->heavy_deg = heavy_deg;
+    s->seg_edges = seg_edges;
+    s->hub_push = hub_push;
+    StepArgs& a = s->args;
+    a.part = s->d_part;
+    a.summary = (const uint32_t*)s->d_summary;
+    a.hub_T = s->d_hub;
+    a.hub_D = hub_push ? s->d_hub + 2 * HU : nullptr;
+    if (hub_push) {
+        a.hub_out_ptr = L->d_hub_out_ptr;
+        a.hub_out_idx = L->d_hub_out_idx;
+        a.hub_base = L->hub_base;
+        a.hub_units = (uint32_t)HU;
+    }
+    a.heavy_first = L->d_heavy_first;
+    a.seg_part = s->d_seg_part;
+    a.heavy_deg = limit;
+    a.seg_edges = seg_edges;
+    a.ldeg = L->d_ldeg;
+    a.chunk_meta = L->d_chunk_meta;
+    a.orig_id = g->d_orig;
+    a.udeg = L->udeg;
+    a.pbits = L->pbits;
+    a.col_t = L->d_col_t;
+    a.w_t = L->d_w_t;
     {
         std::lock_guard<std::mutex> lk(g->layout_mu);
         for (auto it = g->layouts.begin(); it != g->layouts.end();) {
@@ -692,41 +744,34 @@ fs_status apply_bins(fs_sim* s, int32_t heavy_deg, int32_t seg_edges)
             else ++it;
         }
     }
-    s->nseg = L->nseg;
-    s->d_segs = L->d_segs;
-    s->heavy_deg = heavy_deg;
-    s->seg_edges = seg_edges;
-    // binned rows of an unweighted graph with constant shedding take pushed
-    // pressure; the others (and batches of such sims) read segment partials
-    s->hub_push = L->hubs > 0 && s->d_shed[0] == nullptr;
-    if (s->nseg && !s->hub_push)
-        FS_HIP(sim_alloc(s, &s->d_seg_part, (size_t)s->nseg * (size_t)s->R * sizeof(uint32_t)));
-    if (s->hub_push) {
-        const size_t HU = (size_t)L->hubs * (size_t)s->R;
-        FS_HIP(sim_alloc(s, (void**)&s->d_hub, 5 * HU * sizeof(uint32_t)));
-        s->args.hub_T = s->d_hub;
-        s->args.hub_D = s->d_hub + 2 * HU;
-        s->args.hub_out_ptr = L->d_hub_out_ptr;
-        s->args.hub_out_idx = L->d_hub_out_idx;
-        s->args.hub_base = L->hub_base;
-        s->args.hub_units = (uint32_t)HU;
-        FS_HIP(refresh_hubs(s, s->step));
-    }
-    s->args.heavy_first = L->d_heavy_first;
-    s->args.seg_part = s->d_seg_part;
-    s->args.heavy_deg = limit;
-    s->args.seg_edges = seg_edges;
-    s->args.ldeg = L->d_ldeg;
-    s->args.chunk_meta = L->d_chunk_meta;
-    s->args.orig_id = g->d_orig;
-    s->args.udeg = L->udeg;
-    s->args.pbits = L->pbits;
-    if (left_replica_step) FS_HIP(refresh_summary(s)); // (the replica step keeps none)
-    s->kfn = step_fn(s);
-    if (!s->kfn) return fail(FS_ERR_DEVICE, "no step kernel for this configuration");
-    s->args.col_t = L->d_col_t;
-    s->args.w_t = L->d_w_t;
+    FS_HIP(refresh_hubs(s, s->step));
+    // (the other variants and the replica step keep no summary)
+    if (left_replica_step || other_mode) FS_HIP(refresh_summary(s));
     return FS_OK;
+}
+
+fs_status apply_bins(fs_sim* s, int32_t heavy_deg, int32_t seg_edges)
+{
+    return configure(s, s->mode, heavy_deg, seg_edges);
+}
+
+// Whether sim s may run a step variant.  Adaptive sims only move between the
+// LDS variants, which share the workgroup count, so the per-workgroup rate
+// maxima the next step folds keep their meaning.
+fs_status check_variant(const fs_sim* s, int mode)
+{
+    const size_t units = (size_t)s->g->n * (size_t)s->R;
+    if (mode == fsi::MODE_RESIDENT && units > fsi::RESIDENT_BITS)
+        return fail(FS_ERR_INVALID_ARG, "the resident variant holds at most 2^20 units");
+    if (mode == fsi::MODE_STREAM && s->p.adaptive) return fail(FS_ERR_INVALID_ARG, "adaptive sims keep an LDS variant");
+    return FS_OK;
+}
+
+fs_status apply_variant(fs_sim* s, int mode)
+{
+    if (mode == s->mode) return FS_OK;
+    const fs_status st = check_variant(s, mode);
+    return st != FS_OK ? st : configure(s, mode, s->heavy_deg, s->seg_edges);
 }
 
 fs_status use_plain_columns(fs_sim* s)
@@ -734,7 +779,9 @@ fs_status use_plain_columns(fs_sim* s)
     if (!s->pack) return FS_OK;
     s->pack = false;
     if (!s->layout || s->layout->pbits == 0) return FS_OK;
-    return apply_bins(s, s->heavy_deg, s->seg_edges);
+    const fs_status st = apply_bins(s, s->heavy_deg, s->seg_edges);
+    if (st != FS_OK) s->pack = true;
+    return st;
 }
 
 fsi::SumArgs summary_args(const fs_sim* s, uint32_t after)
@@ -944,31 +991,6 @@ fs_status seed_staged(fs_sim* s, int32_t replica, const int64_t* d_nodes, int64_
     return FS_OK;
 }
 
-// Switches sim s to another step variant (mode): workgroup shape and
-// count, count partials, the summary buffer and the kernels.  Adaptive sims
-// only move between the LDS variants, which share the workgroup count, so
-// the per-workgroup rate maxima the next step folds keep their meaning.
-fs_status apply_variant(fs_sim* s, int mode)
-{
-    if (mode == s->mode) return FS_OK;
-    const size_t units = (size_t)s->g->n * (size_t)s->R;
-    if (mode == fsi::MODE_RESIDENT && units > fsi::RESIDENT_BITS)
-        return fail(FS_ERR_INVALID_ARG, "the resident variant holds at most 2^20 units");
-    if (mode == fsi::MODE_STREAM && s->p.adaptive) return fail(FS_ERR_INVALID_ARG, "adaptive sims keep an LDS variant");
-    drop_graph_exec(s);
-    fs_status shst = set_shape(s, mode, s->lgW);
-    if (shst != FS_OK) return shst;
-    if (mode == fsi::MODE_SUMMARY && !s->d_summary)
-        FS_HIP(sim_alloc(s, (void**)&s->d_summary, ((size_t)s->sum_bits + 511) / 512 * 64));
-    s->args.summary = (const uint32_t*)s->d_summary;
-    const bool weighted = s->g->d_weights != nullptr, shed = s->d_shed[0] != nullptr;
-    s->kfn = step_fn(s);
-    s->hfn = fsk::heavy_kernel_fn(weighted, shed, mode == fsi::MODE_RESIDENT);
-    if (!s->kfn || !s->hfn) return fail(FS_ERR_DEVICE, "no step kernel for this configuration");
-    FS_HIP(refresh_summary(s));
-    return FS_OK;
-}
-
 // FNV-1a over a run's signature: what the fastest configuration depends on.
 struct Fnv {
     uint64_t h = 1469598103934665603ull;
@@ -1056,12 +1078,12 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
         int32_t hd = 0, se = 0;
         if (cache_lookup(tp.cache_path, out->signature, &mode, &hd, &se) &&
             (tp.variants || mode == s->mode || (s->stream_too && mode == fsi::MODE_STREAM))) {
-            if (tp.variants) s->stream_too = false;
             FS_HIP(hipStreamSynchronize(s->stream));
-            fs_status st = apply_variant(s, mode);
-            if (st == FS_OK) st = apply_bins(s, hd, se);
+            fs_status st = mode == s->mode ? FS_OK : check_variant(s, mode);
+            if (st == FS_OK) st = configure(s, mode, hd, se);
             if (st != FS_OK) return st;
             FS_HIP(hipStreamSynchronize(s->stream));
+            if (tp.variants) s->stream_too = false;
             out->variant = s->mode + 1;
             out->heavy_degree = s->heavy_deg;
             out->segment_edges = s->seg_edges;
@@ -1129,9 +1151,8 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     int trials = 0;
     for (int m : modes) {
         if (st != FS_OK) break;
-        if ((st = apply_variant(s, m)) != FS_OK) break;
         for (const auto& c : bins) {
-            if ((st = apply_bins(s, c.first, c.second)) != FS_OK) break;
+            if ((st = configure(s, m, c.first, c.second)) != FS_OK) break;
             // (the summary of the restored bitmap)
             if (refresh_summary(s) != hipSuccess) { st = fail(FS_ERR_DEVICE, "summary"); break; }
             // one untimed warm-up step, then the timed trial, then restore
@@ -1170,13 +1191,17 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     for (auto& b : bufs)
         if (b.live) (void)hipMemcpyAsync(b.live, b.copy.p, b.bytes, hipMemcpyDeviceToDevice, s->stream);
     FS_HIP(hipStreamSynchronize(s->stream));
-    if (st != FS_OK) return st;
-    // the choice, on the restored state (bins recount pushed pressure, the
-    // summary is rebuilt from the restored bitmap)
-    if ((st = apply_variant(s, best_mode)) != FS_OK) return st;
-    if ((st = apply_bins(s, best.first, best.second)) != FS_OK) return st;
+    // the choice, or after a failure the configuration of entry, on the
+    // restored state (the pushed pressure is recounted and the summary rebuilt
+    // from the restored bitmap, whichever configuration the sim is left with)
+    const std::string why = g_err;
+    const fs_status end = st == FS_OK ? configure(s, best_mode, best.first, best.second)
+                                      : configure(s, modes[0], bins[0].first, bins[0].second);
+    FS_HIP(refresh_hubs(s, s->step));
     FS_HIP(refresh_summary(s));
     FS_HIP(hipStreamSynchronize(s->stream));
+    if (st != FS_OK) return fail(st, why);
+    if (end != FS_OK) return end;
     if (tp.variants) s->stream_too = false;
     out->variant = s->mode + 1;
     out->heavy_degree = s->heavy_deg;
@@ -1582,13 +1607,7 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
         a.htab_len = fsi::HTAB_LEN;
         a.htab_inv = s->storage == 0 ? 1.0f / a.dt : 1.0f;
     }
-    s->kfn = step_fn(s);
-    s->hfn = fsk::heavy_kernel_fn(g->d_weights != nullptr, shedding, s->mode == fsi::MODE_RESIDENT);
     s->pack = packing_allowed(g, p);
-    if (!s->kfn || !s->hfn) {
-        release_sim(s);
-        return fail(FS_ERR_DEVICE, "no step kernel for this configuration");
-    }
     {
         const int32_t hd = p->heavy_degree == 0 ? 64 : p->heavy_degree;
         const int32_t se = p->segment_edges == 0 ? 512 : p->segment_edges;
