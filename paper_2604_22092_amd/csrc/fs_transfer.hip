@@ -263,6 +263,8 @@ fs_status copy_history(int device, hipStream_t stream, const uint32_t* d_hist, u
         const uint32_t* h = (const uint32_t*)s.host;
         for (size_t j = 0; j < 4 * (size_t)m; ++j) out[4 * at + j] = (int64_t)h[j];
     }
+    // (a failed wait may have left the kernel writing the buffer)
+    if (e != hipSuccess) (void)hipStreamSynchronize(stream);
     give(s);
     FS_HIP(e);
     return FS_OK;

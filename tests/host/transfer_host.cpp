@@ -139,7 +139,17 @@ int main()
             std::puts("per-thread stream: work queued by other threads");
         std::fill(back.begin(), back.end(), -1);
     }
-    fsr::graph_closed();
+    // a read whose event cannot be recorded waits for its kernel before the
+    // pinned buffer goes back to the pool or is freed
+    for (bool keep : {true, false}) {
+        if (!keep) fsr::graph_closed(); // (no graph is open: buffers are freed, not kept)
+        fail_events = 1;
+        int64_t rows[4 * 3];
+        if (fsr::copy_history(0, (hipStream_t)&mu, nullptr, 1, 0, 0, 8, 3, rows) == FS_OK) std::puts("error lost");
+        given_unwaited += unwaited; // (the buffer is free for the next taker now)
+        unwaited = 0;
+    }
+    if (given_unwaited) std::puts("buffer given up under a running kernel");
     std::puts("done");
     return 0;
 }

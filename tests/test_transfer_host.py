@@ -31,3 +31,8 @@ def output(tmp_path_factory):
 def test_per_thread_stream_is_used_by_the_caller_alone(output):
     assert "failed" not in output and "differs" not in output
     assert "per-thread stream" not in output
+
+
+def test_a_failed_history_read_waits_for_its_kernel(output):
+    assert "error lost" not in output
+    assert "buffer given up" not in output
