@@ -70,9 +70,11 @@ __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G
             __syncthreads();
         }
         if (t < C) {
-            if (base)
+            if (base) {
                 __hip_atomic_store(&part[(size_t)j * G * C + t], s[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else
+                // (thread 0's ticket waits for its own wavefront's stores only)
+                __threadfence();
+            } else
                 out[(size_t)((first + j) % H) * C + t] = s[t];
         }
     }
