@@ -15,8 +15,6 @@ constexpr int WG = 256;
 // streaming variant with many replicas leaves up to max_step_grid(R) * 4R
 // partial counts, one block reads them all).
 constexpr int RED_TPB = 1024;
-// Words of step totals its last block holds at a time.
-constexpr int RED_TILE = 4096;
 // Step kernel variants, all walking 64-unit chunks per wavefront:
 //  MODE_STREAM   bitmap read through the caches; STREAM_TPB threads per workgroup;
 //  MODE_RESIDENT the whole bitmap (up to RESIDENT_BITS units) held in LDS;

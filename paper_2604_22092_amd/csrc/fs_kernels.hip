@@ -22,33 +22,88 @@
 
 namespace fsk {
 
+// The counts after each of the r steps, from the counter's value n before them
+// and the slots' totals (the first row of every slot of part); returns the
+// value after them.  Thread t takes counter c = t mod C (replica, compartment),
+// which loses the transitions out of its compartment and gains those into it,
+// in SLOTS consecutive slots at a time, loaded together.  s_wave: RED_TPB words.
+template <uint32_t SLOTS>
+__device__ __forceinline__ uint32_t reduce_prefix(const uint32_t* part, uint32_t G, uint32_t lgC, uint32_t* out, uint32_t H,
+                                                  uint32_t slot0, uint32_t r, uint32_t n, uint32_t* s_wave)
+{
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    const uint32_t C = 1u << lgC, c = t & (C - 1u);
+    const uint32_t wide = C > 64u ? C >> 6 : 1u; // wavefronts that share a slot
+    for (uint32_t r0 = 0; r0 < r; r0 += SLOTS * (RED_TPB >> lgC)) {
+        const uint32_t i0 = r0 + SLOTS * (t >> lgC);
+        uint32_t v[SLOTS];
+#pragma unroll
+        for (uint32_t u = 0; u < SLOTS; ++u)
+            v[u] = i0 + u < r ? __hip_atomic_load(&part[((size_t)(i0 + u) * G << lgC) + c], __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT)
+                              : 0u;
+#pragma unroll
+        for (uint32_t u = 1; u < SLOTS; ++u) v[u] += v[u - 1];
+        // prefix over the wavefront's slots, then over the wavefronts
+        uint32_t x = v[SLOTS - 1];
+        for (uint32_t d = C; d < 64u; d <<= 1) {
+            const uint32_t y = __shfl_up(x, d, 64);
+            if (lane >= d) x += y;
+        }
+        if (lane + C >= 64u) s_wave[(wave << 6) + (c & 63u)] = x; // (its last slots)
+        __syncthreads();
+        uint32_t before = x - v[SLOTS - 1], all = 0u;
+#pragma unroll
+        for (uint32_t w = 0; w < RED_TPB / 64u; ++w) {
+            const uint32_t y = (w & (wide - 1u)) == (wave & (wide - 1u)) ? s_wave[(w << 6) + (c & 63u)] : 0u;
+            all += y;
+            if (w < wave) before += y;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < SLOTS; ++u) {
+            // (C is a multiple of 4: the lane before holds the same slot's counter before)
+            const uint32_t in = __shfl_up(before + v[u], 1, 64);
+            const uint32_t i = i0 + u;
+            if (i < r && (size_t)i + H >= (size_t)r)
+                out[(size_t)((slot0 + i) % H) * C + c] = n + ((c & 3u) != 0u ? in : 0u) - (before + v[u]);
+        }
+        const uint32_t in = __shfl_up(all, 1, 64);
+        n += ((c & 3u) != 0u ? in : 0u) - all;
+        __syncthreads();
+    }
+    return n;
+}
+
 // Sums per-workgroup count partials.  Block j handles slot j: rows of C
 // counters from G workgroups, part[j][g][c]; the totals go to
 // out[((base + j) mod H)][c] where base = ctl->step (0 without ctl).
-// Requires C a power of two <= RED_TPB (C = 4R with R a power of two <= 64).  Each thread keeps eight independent sums of the rows it reads (so
-// eight loads are in flight), and the block's sums are folded by a tree in
-// LDS (integer sums: the order does not change them).
+// Requires C a power of two <= RED_TPB (C = 4R with R a power of two <= 64).
+// Each thread keeps eight independent sums of the rows it reads (so eight loads
+// are in flight), and the block's sums are folded by a tree in LDS (integer
+// sums: the order does not change them).
 // With a ctl, the r blocks of the launch end the launch sequence: each takes
 // a ticket in ctl->done once its reads of ctl->step are done, and the last
 // one adds r to ctl->step and clears the count (so the sequence needs no
 // launch of its own for the advance).
 // With a base, the partials are the step's transitions, [replica][S -> E, E ->
 // I, I -> R, unused]: block j leaves its totals in the first row of
-// slot j, and the last block walks the slots, turning base, the counts before
-// the sequence, into the counts after each step (r additions per counter,
-// against a tally of every unit's state in every step).
+// slot j, and the last block turns base, the counts before the sequence, into
+// the counts after each step (r additions per counter, against a tally of every
+// unit's state in every step) by a prefix sum over the slots (reduce_prefix): one
+// thread per counter going through the slots in turn took longer than the rest
+// of the launch (4 counters, 256 workgroups: 50 slots 9.2 us, 300 slots 34; now
+// 5.2 and 10.5, against 4.1 and 9.2 of sums alone).
 __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G, uint32_t C, uint32_t* out,
                                             uint32_t H, uint32_t j, uint32_t r, uint32_t* base)
 {
     __shared__ uint32_t s[RED_TPB];
-    __shared__ uint32_t s_tile[RED_TILE];
+    __shared__ uint32_t s_wave[RED_TPB];
     __shared__ uint32_t s_last;
     const uint32_t t = threadIdx.x;
     const uint32_t lgC = (uint32_t)__builtin_ctz(C);
     const unsigned long long first = ctl ? ctl->step : 0ull;
     // (every block reads what only the last one uses, before the ticket)
-    uint32_t n = base && t < C ? base[t] : 0u;
-    const uint32_t slot0 = (uint32_t)(first % H);
+    uint32_t n = base ? base[t & (C - 1u)] : 0u;
     // of a sequence longer than the ring only the last H steps are kept, so
     // no two blocks write one slot
     if (base || (size_t)j + H >= (size_t)r) {
@@ -70,10 +125,12 @@ __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G
             __syncthreads();
         }
         if (t < C) {
-            if (base) {
+            if (base && r == 1u) {
+                // (the last block itself: its totals stay in s)
+            } else if (base) {
                 __hip_atomic_store(&part[(size_t)j * G * C + t], s[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 // (thread 0's ticket waits for its own wavefront's stores only)
-                __threadfence();
+                if (C > 64u) __threadfence();
             } else
                 out[(size_t)((first + j) % H) * C + t] = s[t];
         }
@@ -87,31 +144,20 @@ __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G
         __syncthreads();
         if (!s_last) return;
         if (base) {
-            // the slots' totals by tiles of RED_TILE words (loaded together);
-            // thread t < C carries counter t = (replica, compartment): it
-            // loses the transitions out of its compartment and gains those
-            // into it
-            const uint32_t rows = RED_TILE >> lgC;
-            uint32_t slot = slot0; // the ring row of step i
-            for (uint32_t r0 = 0; r0 < r; r0 += rows) {
-                const uint32_t m = min(rows, r - r0);
-#pragma unroll
-                for (uint32_t u = 0; u < RED_TILE / RED_TPB; ++u) {
-                    const uint32_t i = u * RED_TPB + t;
-                    if (i < m << lgC)
-                        s_tile[i] = __hip_atomic_load(&part[((size_t)(r0 + (i >> lgC)) * G << lgC) + (i & (C - 1u))],
-                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                __syncthreads();
+            // counter c = (replica, compartment) loses the transitions out of
+            // its compartment and gains those into it
+            const uint32_t c = t & (C - 1u);
+            // (a 64-bit division takes as long as a load)
+            const uint32_t slot0 = (H & (H - 1u)) == 0u ? (uint32_t)first & (H - 1u) : (uint32_t)(first % H);
+            if (r == 1u) {
                 if (t < C) {
-#pragma unroll 8
-                    for (uint32_t i = 0; i < m; ++i) {
-                        n += ((t & 3u) != 0u ? s_tile[i * C + t - 1u] : 0u) - s_tile[i * C + t];
-                        if ((size_t)(r0 + i) + H >= (size_t)r) out[(size_t)slot * C + t] = n;
-                        slot = slot + 1u == H ? 0u : slot + 1u;
-                    }
+                    n += ((c & 3u) != 0u ? s[c - 1u] : 0u) - s[c];
+                    out[(size_t)slot0 * C + c] = n;
                 }
-                __syncthreads();
+            } else {
+                // few slots: one per thread, whose rows a wavefront writes side by side
+                n = r <= RED_TPB >> lgC ? reduce_prefix<1>(part, G, lgC, out, H, slot0, r, n, s_wave)
+                                        : reduce_prefix<4>(part, G, lgC, out, H, slot0, r, n, s_wave);
             }
             if (t < C) base[t] = n;
         }
