@@ -124,6 +124,7 @@ struct StepArgs {
     int32_t n;
     int32_t lgR;          // R = 1 << lgR replicas
     uint32_t step_off;    // j: this launch runs step ctl->step + j, partial slot j
+    uint32_t tpb;         // threads per workgroup of the launch
     // MODE_SUMMARY: one summary bit per group of 32 * 2^sum_shift units
     // (2^sum_shift 32-bit bitmap words)
     int32_t sum_shift;

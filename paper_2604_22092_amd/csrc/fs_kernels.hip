@@ -155,9 +155,11 @@ __device__ __forceinline__ void reduce_body(Ctl* ctl, uint32_t* part, uint32_t G
                     out[(size_t)slot0 * C + c] = n;
                 }
             } else {
-                // few slots: one per thread, whose rows a wavefront writes side by side
-                n = r <= RED_TPB >> lgC ? reduce_prefix<1>(part, G, lgC, out, H, slot0, r, n, s_wave)
-                                        : reduce_prefix<4>(part, G, lgC, out, H, slot0, r, n, s_wave);
+                // (few slots: one per thread, whose rows a wavefront writes side by side)
+                const uint32_t rows = RED_TPB >> lgC;
+                n = r <= rows       ? reduce_prefix<1>(part, G, lgC, out, H, slot0, r, n, s_wave)
+                    : r <= 4 * rows ? reduce_prefix<4>(part, G, lgC, out, H, slot0, r, n, s_wave)
+                                    : reduce_prefix<16>(part, G, lgC, out, H, slot0, r, n, s_wave);
             }
             if (t < C) base[t] = n;
         }

@@ -540,14 +540,19 @@ int replica_width(const fs_graph* g, const fs_sim_params& p, int lgR, int32_t li
 // its own: a small sim's launch is one pass, and four wavefronts that share a
 // SIMD take it in turn (regular d = 10, N = 1e4, 157 chunks: 10 workgroups of
 // 1024 threads 4.2 us per step, 157 of 64 threads 3.7; N = 1e5, 1563 chunks: 98 of
-// 1024 4.5, 196 of 512 4.1).
+// 1024 4.5, 196 of 512 4.1).  Past four wavefronts they come in fours, the same
+// number on every SIMD (d = 8, N = 4e4, R = 4, 2500 chunks: 157 of 1024 4.8, 209 of
+// 768 4.2; N = 6e4, R = 4, 3750 chunks: 235 of 1024 4.6, 250 of 960 4.7).
 void step_shape(const fs_sim* s, int mode, int lgW, uint32_t* tpb, uint32_t* G)
 {
     const size_t chunks = ((size_t)s->g->n * (size_t)s->R + 63) / 64;
     const bool stream = lgW >= 0 || mode == fsi::MODE_STREAM;
     *tpb = fsi::STREAM_TPB;
-    if (!stream)
-        for (*tpb = 64; *tpb < (uint32_t)fsi::RESIDENT_TPB && (size_t)s->cus * (*tpb / 64) < chunks;) *tpb *= 2;
+    if (!stream) {
+        size_t waves = (chunks + s->cus - 1) / s->cus;
+        if (waves > 4) waves = (waves + 3) / 4 * 4;
+        *tpb = 64u * (uint32_t)std::max<size_t>(1, std::min<size_t>(waves, fsi::RESIDENT_TPB / 64));
+    }
     const size_t waves = lgW >= 0 ? (chunks + ((size_t)1 << lgW) - 1) >> lgW : chunks;
     const size_t tiles = (waves + *tpb / 64 - 1) / (*tpb / 64); // workgroups with work
     *G = (uint32_t)std::min<size_t>(tiles, stream ? fsi::max_step_grid(s->R) : s->cus);
@@ -717,6 +722,7 @@ fs_status configure(fs_sim* s, int mode, int32_t heavy_deg, int32_t seg_edges)
     s->hub_push = hub_push;
     StepArgs& a = s->args;
     a.part = s->d_part;
+    a.tpb = tpb;
     a.summary = (const uint32_t*)s->d_summary;
     a.hub_T = s->d_hub;
     a.hub_D = hub_push ? s->d_hub + 2 * HU : nullptr;

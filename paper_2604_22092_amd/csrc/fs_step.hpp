@@ -859,8 +859,15 @@ __device__ __forceinline__ float pressure_heavy(const StepArgs& a, uint32_t node
 // of once per chunk (a chunk of 64 units holds a few).  Per step, drawn chunk by
 // chunk and queued: regular d = 10, N = 1e6 10.3 / 9.6 us; adaptive
 // Erdos-Renyi 8, N = 1e6 17.5 / 15.4; weighted Erdos-Renyi 10, N = 2e5, R = 4
-// 19.1 / 17.4; regular d = 8, N = 1e7 compact 79 / 73.  Wavefronts of a single
-// chunk only pay the way through LDS (regular d = 8, N = 6e4, R = 4: 4.6 / 5.0).
+// 19.1 / 17.4; regular d = 8, N = 1e7 compact 79 / 73.  Where every wavefront has
+// a single chunk, there is nothing to share and the way through LDS, the second
+// age store and the atomic only lengthen the launch's one chain of latencies:
+// uniform layouts then draw in place (regular d = 8, N = 6e4, R = 4: queued 5.0 us,
+// in place 4.6; N = 1.6e5, R = 1 4.8 / 4.4).  Mixed layouts, whose gather takes
+// longer and whose draws are keyed through a table, queue them all the same
+// (Erdos-Renyi 10, N = 3e4, R = 4: drawn chunk by chunk 9.1, queued 7.8, in place
+// 7.9).  Laws are evaluated out of the hot path's way: fixed steps nearly always
+// find their hazards in the table (N = 6e4, R = 4: evaluated in line 4.8).
 // Pooling what a workgroup's wavefronts have left costs a barrier and a
 // search, more than the rounds it saves (N = 1e6 9.6 / 10.0).
 //  q[i].x: the rate, or the age of a unit whose hazard is yet to be evaluated;
@@ -873,7 +880,22 @@ struct DrawCtx {
     uint32_t n;          // queued (wave-uniform)
     uint32_t pass;       // passes begun
     uint32_t wave, nwaves;
+    bool single;         // every wavefront has at most one chunk
 };
+
+// The draw of one unit: Bernoulli tau-leap, fire when u < 1 - exp(-lambda dt).
+__device__ __forceinline__ bool draw_unit(const StepArgs& a, uint32_t id, uint32_t k, uint32_t rep, float lam, float dt)
+{
+    // the key and step pass through an empty asm here, so the round keys
+    // and the key-step terms are formed by scalar adds at each draw
+    // instead of being hoisted out of the walk, where they would take 20
+    // scalar registers and be spilled to vector lanes
+    uint32_t k0 = __builtin_amdgcn_readfirstlane(a.key0), k1 = __builtin_amdgcn_readfirstlane(a.key1),
+             ks = __builtin_amdgcn_readfirstlane(k);
+    asm volatile("" : "+s"(k0), "+s"(k1), "+s"(ks));
+    const uint32_t w = fsd::philox4x32_10(make_uint4(id, ks, rep, 0u), k0, k1).x >> 8;
+    return fsd::bernoulli((float)w * 0x1p-24f, lam * dt);
+}
 
 // Draws the last m (<= 64) queued units, one per lane: Bernoulli tau-leap, fire
 // when u < 1 - exp(-lambda dt), and the transitions of those that fire.  Their
@@ -904,20 +926,14 @@ __device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32
         unit = (c << 6) + (e.y & 63u);
         const uint32_t id = UNIFORM ? unit >> a.lgR : (uint32_t)opaque_uniform(a.orig_id)[unit >> a.lgR];
         float lam = __uint_as_float(e.x);
-        if (e.y & DRAW_EVAL) {
+        const bool eval = (e.y & DRAW_EVAL) != 0u;
+        if (__builtin_expect(__ballot(eval) != 0ull, 0) && eval) {
             lam = unit_hazard(a.hz_dev, a.same_kind, lam, x == (uint32_t)ST_I);
+            asm volatile("" : "+v"(lam)); // (no pending load leaves the branch)
             if (EXTRA && a.rates) a.rates[unit] = lam;
             lmax = fmaxf(lmax, lam);
         }
-        // the key and step pass through an empty asm here, so the round keys
-        // and the key-step terms are formed by scalar adds at each draw
-        // instead of being hoisted out of the walk, where they would take 20
-        // scalar registers and be spilled to vector lanes
-        uint32_t k0 = __builtin_amdgcn_readfirstlane(a.key0), k1 = __builtin_amdgcn_readfirstlane(a.key1),
-                 ks = __builtin_amdgcn_readfirstlane(k);
-        asm volatile("" : "+s"(k0), "+s"(k1), "+s"(ks));
-        const uint32_t w = fsd::philox4x32_10(make_uint4(id, ks, unit & (R - 1), 0u), k0, k1).x >> 8;
-        fire = fsd::bernoulli((float)w * 0x1p-24f, lam * dt);
+        fire = draw_unit(a, id, k, unit & (R - 1), lam, dt);
     }
     if (__ballot(fire) == 0ull) return;
     if (fire) {
@@ -949,18 +965,20 @@ __device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32
     }
 }
 
-// Everything of one pass after its loads were issued but the draws: rates
-// (gather, hazards), the ages and infectivity words of the units that do not
-// fire, (with SHED) the next s(tau) of the infectious units, the queue of the
-// draws, and the chunk's live flag for compaction.
-template <int STORAGE, bool WEIGHTED, int MODE, int UD, bool SHED, bool EXTRA, int PB, class age_t>
+// Everything of one pass after its loads were issued but the queued draws: rates
+// (gather, hazards), the draws made in place (a wavefront's first and only pass)
+// or their queue, the ages and infectivity words of the units that have not
+// fired, (with SHED) the next s(tau) of the infectious units, and the chunk's live
+// flag for compaction.
+template <int STORAGE, bool WEIGHTED, int MODE, int UD, bool SHED, bool EXTRA, int PB, bool FIRST, class age_t>
 __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t>& P, uint32_t lane,
                                              const uint32_t* __restrict__ s_bits, rsrc_t gbits, rsrc_t shedr,
                                              void* __restrict__ shed_out, const ShedPre& sv, const ShedDev& sdv,
-                                             unsigned long long* __restrict__ bits_out, float dt, float& lmax,
-                                             const HubCtx& H, DrawCtx& Q)
+                                             unsigned long long* __restrict__ bits_out, uint32_t k, uint32_t* s_cnt,
+                                             float dt, float& lmax, const HubCtx& H, DrawCtx& Q)
 {
     constexpr bool UNIFORM = UD != 0;
+    using state_t = typename Store<STORAGE>::state_t;
     const uint32_t R = 1u << a.lgR;
 #pragma unroll
     for (int u = 0; u < CU; ++u) {
@@ -1000,8 +1018,26 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
         if (hit) lam = x == ST_I ? P.tab[u][2] : P.tab[u][1];
         const bool miss = ei && !hit;
 
-        // 3.-4. the draws (no draw at lambda = 0)
-        const bool need = miss || lam > 0.0f;
+        // 3.-4. the draws (no draw at lambda = 0): in place, or queued
+        bool fire = false;
+        const bool here = UNIFORM && FIRST && Q.single;
+        if (here && __builtin_expect(__ballot(miss) != 0ull, 0)) {
+            if (miss) {
+                lam = unit_hazard(a.hz_dev, a.same_kind, age_units(ag), x == ST_I);
+                asm volatile("" : "+v"(lam)); // (no pending load leaves the branch)
+            }
+        }
+        if (here && lam > 0.0f) {
+            fire = draw_unit(a, unit >> a.lgR, k, unit & (R - 1), lam, dt);
+        }
+        if (here && __ballot(fire) != 0ull) {
+            if (fire) {
+                opaque_uniform((state_t*)a.state)[unit] = (state_t)(x + 1);
+                atomicAdd(&s_cnt[(unit & (R - 1)) * 4u + (uint32_t)x], 1u); // LDS
+            }
+        }
+        const int xn = x + (fire ? 1 : 0);
+        const bool need = !here && (miss || lam > 0.0f);
         const unsigned long long nm = __ballot(need);
         if (need)
             Q.q[Q.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u))] =
@@ -1010,15 +1046,15 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
         Q.n += (uint32_t)__popcll(nm);
         lmax = fmaxf(lmax, lam);
 
-        // 5.-6. the age of a unit that does not fire (the chunk's descriptors
-        // drop the lanes past its valid units)
-        const age_t an = age_next(ag, dt);
+        // 5.-6. the age of a unit that has not fired here (the chunk's
+        // descriptors drop the lanes past its valid units)
+        const age_t an = fire ? (age_t)0 : age_next(ag, dt);
         BufIO<age_t>::st(make_rsrc((age_t*)a.age + u0, P.nvalid[u] * sizeof(age_t)), lane, age_to_raw(an));
         // the rates, when recorded (EXTRA kernels)
         if (EXTRA && a.rates) st32(make_rsrc(a.rates + u0, P.nvalid[u] * 4u), lane << 2, __float_as_uint(lam));
         // 7. next-step infectivity bits (one 64-bit word per chunk, written by
         // lanes 0 and 1)
-        const unsigned long long mI = __ballot(valid && x == ST_I);
+        const unsigned long long mI = __ballot(valid && xn == ST_I);
         if (UNIFORM) {
             st32(make_rsrc(bits_out + P.chk[u], P.live[u] ? 8u : 0u), lane < 2 ? lane << 2 : OOB,
                  lane == 0 ? (uint32_t)mI : (uint32_t)(mI >> 32));
@@ -1037,9 +1073,9 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
                                                  lane == 0 ? 0 : (int)OOB, 0, 0);
         }
         if (SHED) {
-            // 7'. infectivity values s(tau') of the units that stay infectious
-            // (Eq. (infectivity))
-            const bool inf = valid && x == ST_I;
+            // 7'. infectivity values s(tau') of the infectious units (Eq.
+            // (infectivity); a unit whose queued draw fires gets its own there)
+            const bool inf = valid && xn == ST_I;
             float v = 0.0f;
             if (inf) {
                 v = fsd::shed(sdv, age_units(an));
@@ -1063,7 +1099,8 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
 //    gather reads the global bitmap only where the summary bit is set (when
 //    infection is sparse most neighbours fall in empty groups);
 //  MODE_STREAM: gathers read the bitmap through the caches.
-// The LDS variants run one workgroup of RESIDENT_TPB threads per compute unit.
+// The LDS variants run at most one workgroup per compute unit, of 64 to
+// RESIDENT_TPB threads (StepArgs::tpb).
 template <int STORAGE, bool WEIGHTED, int MODE, int UD, bool SHED, bool EXTRA, int TPB, int PB = 0>
 __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uint32_t nblocks)
 {
@@ -1084,7 +1121,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     __shared__ uint32_t s_px[HUBS ? NW : 1][HUBS ? 64 : 1];
 
     // (a workgroup of the LDS variants may have fewer threads than TPB)
-    const uint32_t tid = threadIdx.x, tpb = USE_LDS ? blockDim.x : (uint32_t)TPB, nw = tpb / 64;
+    const uint32_t tid = threadIdx.x, tpb = USE_LDS ? a.tpb : (uint32_t)TPB, nw = tpb / 64;
     const uint32_t lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform, in a scalar register
     const uint32_t R = 1u << a.lgR;
@@ -1188,7 +1225,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     }
     issue_table<UNIFORM>(a, tv, P, lane);
 
-    DrawCtx Q{s_draw[wave], 0u, 0u, wave_id, nwaves};
+    DrawCtx Q{s_draw[wave], 0u, 0u, wave_id, nwaves, walk <= nwaves};
     // whole wavefronts of draws, and after the wavefront's last pass the rest
     auto draws = [&](bool last) {
         while (Q.n >= (last ? 1u : 64u))
@@ -1211,8 +1248,9 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         if (PREFETCH)
             issue_pass<STORAGE, UD, EXTRA, PB>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P1,
                                                 ahead, H);
-        process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB>(a, P, lane, s_bits, gbits, shedr, shed_out, sv,
-                                                                    sdv, bo, dt, lmax, H, Q);
+        process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, true>(a, P, lane, s_bits, gbits, shedr, shed_out,
+                                                                          sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax, H,
+                                                                          Q);
         first += stride;
         draws(first >= walk);
         if (first >= walk) break;
@@ -1223,8 +1261,9 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         if (PREFETCH)
             issue_pass<STORAGE, UD, EXTRA, PB>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P,
                                                 ahead, H);
-        process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB>(a, P1, lane, s_bits, gbits, shedr, shed_out, sv,
-                                                                    sdv, bo, dt, lmax, H, Q);
+        process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, false>(a, P1, lane, s_bits, gbits, shedr, shed_out,
+                                                                           sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax,
+                                                                           H, Q);
         first += stride;
         draws(first >= walk);
         if (!PREFETCH && first < walk)
