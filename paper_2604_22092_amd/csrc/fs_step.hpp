@@ -281,6 +281,7 @@ struct Pass {
     uint32_t chk[CU], base[CU], ud[CU], nvalid[CU];
     bool live[CU];
     uint32_t xr[CU], agw[CU], dgr[CU];
+    uint32_t org[CU]; // the caller's node id (mixed layouts that draw in place)
     int32_t c[CU][UMAX];
     float tab[CU][3]; // hazard-table entry of the lane's age (issue_table)
     uint32_t ht[CU], hd[CU]; // pushed pressure of a binned unit: count of the last step, delta
@@ -469,7 +470,7 @@ struct Ahead {
 // mixed layout's chunk comes the same way (without compaction): loaded in
 // this pass's issue it would hold the issue up, the column loads depending
 // on it, until every older load (the pass being processed) had arrived.
-template <int STORAGE, int UD, bool EXTRA, int PB, class age_t>
+template <int STORAGE, int UD, bool EXTRA, int PB, bool ORG, class age_t>
 __device__ __forceinline__ void issue_pass(const StepArgs& a, uint32_t first, uint32_t nwaves, uint32_t stride,
                                            uint32_t nchunks, uint32_t walk, uint32_t total, uint32_t lane,
                                            Pass<age_t>& P, Ahead& ah, const HubCtx& H)
@@ -516,6 +517,7 @@ __device__ __forceinline__ void issue_pass(const StepArgs& a, uint32_t first, ui
         // (uniform layouts have no heavy rows and arithmetic metadata: the
         // degree array is not needed)
         P.dgr[u] = UNIFORM ? 0u : BufIO<uint16_t>::ld(make_rsrc(a.ldeg + n0, nrows * 2u), q);
+        if (ORG) P.org[u] = ld32(make_rsrc(a.orig_id + n0, nrows * 4u), q << 2);
         // binned rows with pushed pressure are the nodes from hub_base on:
         // their last count and this step's delta come with the pass
         if (!UNIFORM && H.on) {
@@ -858,21 +860,26 @@ __device__ __forceinline__ float pressure_heavy(const StepArgs& a, uint32_t node
 // hazards no table holds are evaluated once per 64 units that need them instead
 // of once per chunk (a chunk of 64 units holds a few).  Per step, drawn chunk by
 // chunk and queued: regular d = 10, N = 1e6 10.3 / 9.6 us; adaptive
-// Erdos-Renyi 8, N = 1e6 17.5 / 15.4; weighted Erdos-Renyi 10, N = 2e5, R = 4
-// 19.1 / 17.4; regular d = 8, N = 1e7 compact 79 / 73.  Where every wavefront has
-// a single chunk, there is nothing to share and the way through LDS, the second
-// age store and the atomic only lengthen the launch's one chain of latencies:
-// uniform layouts then draw in place (regular d = 8, N = 6e4, R = 4: queued 5.0 us,
+// Erdos-Renyi 8, N = 1e6 17.5 / 15.4; regular d = 8, N = 1e7 compact 79 / 73.
+// Where every wavefront has a single chunk, there is nothing to share and the way
+// through LDS, the second age store and the atomic only lengthen the launch's one
+// chain of latencies: uniform layouts then draw in place (regular d = 8, N = 6e4, R = 4: queued 5.0 us,
 // in place 4.6; N = 1.6e5, R = 1 4.8 / 4.4).  Mixed layouts, whose gather takes
 // longer and whose draws are keyed through a table, queue them all the same
 // (Erdos-Renyi 10, N = 3e4, R = 4: drawn chunk by chunk 9.1, queued 7.8, in place
 // 7.9).  Laws are evaluated out of the hot path's way: fixed steps nearly always
 // find their hazards in the table (N = 6e4, R = 4: evaluated in line 4.8).
+// Weighted kernels and shedding ones, which spend the pass on the gather's loads,
+// draw in place always (queued / in place: weighted Erdos-Renyi 10, N = 1.5e6 65.0 /
+// 63.6 us, N = 1e5 7.1 / 6.9; weighted Barabasi-Albert 4, N = 1.5e6 66.7 / 64.5;
+// shedding, regular d = 13, N = 1.5e6 77.8 / 74.6, N = 3e5 14.0 / 13.7; weighted
+// Erdos-Renyi 10, N = 2e5, R = 4, an exception, 18.2 / 18.5).
 // Pooling what a workgroup's wavefronts have left costs a barrier and a
 // search, more than the rounds it saves (N = 1e6 9.6 / 10.0).
 //  q[i].x: the rate, or the age of a unit whose hazard is yet to be evaluated;
 //  q[i].y: lane | pass << 6 | state << 29 | DRAW_EVAL, the pass's chunk being
 //          that of walk position wave + pass * waves.
+constexpr bool draws_in_place(bool weighted, bool shed) { return weighted || shed; }
 constexpr uint32_t DRAWQ = 128; // at most 63 left over plus one pass's 64
 constexpr uint32_t DRAW_EVAL = 0x80000000u;
 struct DrawCtx {
@@ -903,10 +910,10 @@ __device__ __forceinline__ bool draw_unit(const StepArgs& a, uint32_t id, uint32
 // the states before the step: a unit that fires overwrites its age (stores of
 // one wavefront to one address keep their order) and flips its bit (in the L2
 // that holds the word: no other compute unit touches it in this launch).
-template <int STORAGE, bool UNIFORM, bool SHED, bool EXTRA, bool HUBS>
+template <int STORAGE, bool UNIFORM, bool EXTRA, bool HUBS>
 __device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32_t m, uint32_t lane, uint32_t k,
-                                           uint32_t* __restrict__ bits_out, void* shed_out, const ShedDev& sdv,
-                                           uint32_t* s_cnt, float dt, float& lmax, HubCtx& H)
+                                           uint32_t* __restrict__ bits_out, uint32_t* s_cnt, float dt, float& lmax,
+                                           HubCtx& H)
 {
     using state_t = typename Store<STORAGE>::state_t;
     using age_t = typename Store<STORAGE>::age_t;
@@ -942,12 +949,6 @@ __device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32
         atomicAdd(&s_cnt[(unit & (R - 1)) * 4u + x], 1u); // LDS
         if (x != (uint32_t)ST_S)
             __hip_atomic_fetch_xor(&bits_out[unit >> 5], 1u << (unit & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (SHED && x == (uint32_t)ST_E) {
-            // newly infectious: s at age 0
-            const float v = fsd::shed(sdv, 0.0f);
-            if (STORAGE == 0) ((float*)shed_out)[unit] = v;
-            else ((uint16_t*)shed_out)[unit] = (uint16_t)float_to_half_bits(v);
-        }
     }
     if (HUBS && H.on) {
         // a unit entering or leaving I is queued for its pushes into the
@@ -966,7 +967,7 @@ __device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32
 }
 
 // Everything of one pass after its loads were issued but the queued draws: rates
-// (gather, hazards), the draws made in place (a wavefront's first and only pass)
+// (gather, hazards), the draws made in place (draws_in_place, or a wavefront's only pass)
 // or their queue, the ages and infectivity words of the units that have not
 // fired, (with SHED) the next s(tau) of the infectious units, and the chunk's live
 // flag for compaction.
@@ -1020,7 +1021,7 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
 
         // 3.-4. the draws (no draw at lambda = 0): in place, or queued
         bool fire = false;
-        const bool here = UNIFORM && FIRST && Q.single;
+        const bool here = draws_in_place(WEIGHTED, SHED) || (UNIFORM && FIRST && Q.single);
         if (here && __builtin_expect(__ballot(miss) != 0ull, 0)) {
             if (miss) {
                 lam = unit_hazard(a.hz_dev, a.same_kind, age_units(ag), x == ST_I);
@@ -1028,7 +1029,7 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
             }
         }
         if (here && lam > 0.0f) {
-            fire = draw_unit(a, unit >> a.lgR, k, unit & (R - 1), lam, dt);
+            fire = draw_unit(a, UNIFORM ? unit >> a.lgR : P.org[u], k, unit & (R - 1), lam, dt);
         }
         if (here && __ballot(fire) != 0ull) {
             if (fire) {
@@ -1073,8 +1074,8 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
                                                  lane == 0 ? 0 : (int)OOB, 0, 0);
         }
         if (SHED) {
-            // 7'. infectivity values s(tau') of the infectious units (Eq.
-            // (infectivity); a unit whose queued draw fires gets its own there)
+            // 7'. infectivity values s(tau') of the units infectious after the
+            // step (Eq. (infectivity))
             const bool inf = valid && xn == ST_I;
             float v = 0.0f;
             if (inf) {
@@ -1106,6 +1107,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
 {
     constexpr bool UNIFORM = UD != 0;
     constexpr bool USE_LDS = MODE != MODE_STREAM;
+    constexpr bool IN_PLACE = draws_in_place(WEIGHTED, SHED), ORG = IN_PLACE && !UNIFORM;
     using age_t = typename Store<STORAGE>::age_t;
     constexpr int NW = TPB / 64;
     static_assert(PB == 0 || !WEIGHTED, "packed columns: unit weights only");
@@ -1113,7 +1115,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     __shared__ uint32_t s_cnt[4 * 64];
     __shared__ __attribute__((aligned(16))) uint32_t s_bits[USE_LDS ? RESIDENT_BITS / 32 : 4];
     static_assert(SUMMARY_BITS <= RESIDENT_BITS, "the summary shares the LDS bitmap array");
-    __shared__ uint2 s_draw[NW][DRAWQ];
+    __shared__ uint2 s_draw[IN_PLACE ? 1 : NW][IN_PLACE ? 1 : DRAWQ];
     // pushed pressure of binned rows: per-wavefront push queue and flush tables
     constexpr bool HUBS = !UNIFORM && !WEIGHTED && !SHED;
     __shared__ uint32_t s_pq[HUBS ? NW : 1][HUBS ? PUSHQ : 1];
@@ -1188,7 +1190,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
             ahead.my[u] = m.y;
         }
     }
-    issue_pass<STORAGE, UD, EXTRA, PB>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
+    issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
     for (uint32_t i = tid; i < 4 * R; i += tpb) s_cnt[i] = 0;
     if (USE_LDS) {
         // 16 bytes per lane straight into LDS: wave w fills the blocks of 64
@@ -1225,12 +1227,13 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     }
     issue_table<UNIFORM>(a, tv, P, lane);
 
-    DrawCtx Q{s_draw[wave], 0u, 0u, wave_id, nwaves, walk <= nwaves};
+    DrawCtx Q{s_draw[IN_PLACE ? 0 : wave], 0u, 0u, wave_id, nwaves, walk <= nwaves};
     // whole wavefronts of draws, and after the wavefront's last pass the rest
     auto draws = [&](bool last) {
-        while (Q.n >= (last ? 1u : 64u))
-            draw_batch<STORAGE, UNIFORM, SHED, EXTRA, HUBS>(a, Q, min(Q.n, 64u), lane, (uint32_t)k, (uint32_t*)bo,
-                                                            shed_out, sdv, s_cnt, dt, lmax, H);
+        if constexpr (!IN_PLACE)
+            while (Q.n >= (last ? 1u : 64u))
+                draw_batch<STORAGE, UNIFORM, EXTRA, HUBS>(a, Q, min(Q.n, 64u), lane, (uint32_t)k, (uint32_t*)bo, s_cnt,
+                                                          dt, lmax, H);
     };
     static_assert(CU == 1, "walk position of a queued draw: one chunk per pass");
 
@@ -1246,8 +1249,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         if (first >= walk) break;
         if (SPLIT) shed_pre<STORAGE, UD, PB>(a, P, lane, s_bits, shedr, sv);
         if (PREFETCH)
-            issue_pass<STORAGE, UD, EXTRA, PB>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P1,
-                                                ahead, H);
+            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P1,
+                                                     ahead, H);
         process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, true>(a, P, lane, s_bits, gbits, shedr, shed_out,
                                                                           sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax, H,
                                                                           Q);
@@ -1255,11 +1258,11 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         draws(first >= walk);
         if (first >= walk) break;
         if (!PREFETCH)
-            issue_pass<STORAGE, UD, EXTRA, PB>(a, first, nwaves, stride, nchunks, walk, total, lane, P1, ahead, H);
+            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P1, ahead, H);
         issue_table<UNIFORM>(a, tv, P1, lane);
         if (SPLIT) shed_pre<STORAGE, UD, PB>(a, P1, lane, s_bits, shedr, sv);
         if (PREFETCH)
-            issue_pass<STORAGE, UD, EXTRA, PB>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P,
+            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P,
                                                 ahead, H);
         process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, false>(a, P1, lane, s_bits, gbits, shedr, shed_out,
                                                                            sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax,
@@ -1267,7 +1270,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
         first += stride;
         draws(first >= walk);
         if (!PREFETCH && first < walk)
-            issue_pass<STORAGE, UD, EXTRA, PB>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
+            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
         if (first < walk) issue_table<UNIFORM>(a, tv, P, lane);
     }
 
