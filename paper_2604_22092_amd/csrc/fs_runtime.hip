@@ -1013,7 +1013,9 @@ uint64_t tune_signature(const fs_sim* s)
 {
     const fs_graph* g = s->g;
     Fnv f;
-    const char* ver = "flashspread-tune-1";
+    // (raised when what a choice is worth changes: choices timed with other step
+    // kernels, or bins that would now leave the replica step, are made anew)
+    const char* ver = "flashspread-tune-2";
     f.add(ver, std::strlen(ver));
     int cus = 0;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device);
