@@ -1127,7 +1127,7 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     }
     // candidates: the entry configuration first, then the other variants and bins
     std::vector<int> modes{s->mode};
-    if (tp.variants && s->lgW < 0) { // (the replica step is the same in every variant)
+    if (tp.variants) {
         for (int m : {fsi::MODE_RESIDENT, fsi::MODE_SUMMARY, fsi::MODE_STREAM}) {
             if (m == s->mode) continue;
             if (m == fsi::MODE_RESIDENT && units > fsi::RESIDENT_BITS) continue;
@@ -1160,6 +1160,8 @@ fs_status autotune(fs_sim* s, const fs_tune_params& tp, fs_tune_result* out)
     for (int m : modes) {
         if (st != FS_OK) break;
         for (const auto& c : bins) {
+            // (the replica step is the same in every variant)
+            if (m != modes[0] && replica_width(s->g, s->p, s->lgR, light_limit(c.first)) >= 0) continue;
             if ((st = configure(s, m, c.first, c.second)) != FS_OK) break;
             // (the summary of the restored bitmap)
             if (refresh_summary(s) != hipSuccess) { st = fail(FS_ERR_DEVICE, "summary"); break; }

@@ -1,5 +1,6 @@
-"""The autotuner's saved choices: those saved by a version whose step kernels
-were others are made anew."""
+"""The autotuner's saved choices and candidates: choices saved by a version
+whose step kernels were others are made anew, and bins that leave the replica
+step are tried in every variant."""
 import numpy as np
 import pytest
 import torch  # (at collection, before any test loads the library: one HIP runtime for both)
@@ -47,3 +48,26 @@ def test_an_older_choice_is_made_anew(tmp_path):
         assert again.autotune(3, variants=True, cache_path=path)["from_cache"]
         sim.close()
         again.close()
+
+
+def test_bins_that_leave_the_replica_step_are_tried_in_every_variant():
+    rp, ci = W.barabasi_albert(140_000, 5, 2)
+    top = int(np.diff(rp).max())
+    assert top > 256
+    bins = [64, -1] + [t for t in (8, 12, 16, 24, 32, 128, 256) if t < top]
+    leaving = [b for b in bins if b < 0 or b > 127]
+    with fs.Graph(rp, ci) as g:
+        sim = fs.Sim.from_model(g, MODEL, replicas=4)
+        ref = fs.Sim.from_model(g, MODEL, replicas=4)
+        for s in (sim, ref):
+            s.seed(np.arange(200), replica=-1)
+        res = sim.autotune(3, variants=True)
+        # (560000 units: resident, summary and streaming)
+        assert res["trials"] == len(bins) + 2 * len(leaving)
+        sim.step(20)
+        ref.step(20)
+        for r in range(4):
+            np.testing.assert_array_equal(sim.history(0, 20, r), ref.history(0, 20, r))
+            np.testing.assert_array_equal(sim.get_state(r)[0], ref.get_state(r)[0])
+        sim.close()
+        ref.close()
