@@ -4,9 +4,10 @@ general step and the FP64 oracle.
 Sims of at least 8192 chunks of 64 units take it; one that records its rates
 takes the general kernel, so the two run side by side from the same states.
 States, ages and counts must be identical (integer pressures, the same FP32
-rates, the same draws).  The cases sit around the sizes where the groups get
-wider (3072 groups of 8 and 16 chunks), their remainders, rows of mixed, odd,
-zero and the largest counted degree, and binned rows.
+rates, the same draws).  The cases run groups of 4 and of 8 chunks, on both sides
+of the size where 8 take over (3072 of them), their remainders, rows of mixed,
+odd, zero and the largest counted degree, and binned rows; groups of 16 are
+tested in a file of their own.
 """
 import numpy as np
 import pytest
