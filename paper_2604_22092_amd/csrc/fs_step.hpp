@@ -5,6 +5,8 @@
 // other, so the two compile in parallel).
 #pragma once
 
+#include <type_traits>
+
 #include <hip/hip_runtime.h>
 
 #include "fs_device.hpp"
@@ -873,13 +875,23 @@ __device__ __forceinline__ float pressure_heavy(const StepArgs& a, uint32_t node
 // draw in place always (queued / in place: weighted Erdos-Renyi 10, N = 1.5e6 65.0 /
 // 63.6 us, N = 1e5 7.1 / 6.9; weighted Barabasi-Albert 4, N = 1.5e6 66.7 / 64.5;
 // shedding, regular d = 13, N = 1.5e6 77.8 / 74.6, N = 3e5 14.0 / 13.7; weighted
-// Erdos-Renyi 10, N = 2e5, R = 4, an exception, 18.2 / 18.5).
+// Erdos-Renyi 10, N = 2e5, R = 4, an exception, 18.2 / 18.5), and so do streaming
+// ones, whose sims with several replicas have one or two chunks per wavefront and
+// those with many waited for the gather (200 steps of regular d = 10, R = 8, 16500
+// chunks 3.36 / 2.95 ms, 25000 3.87 / 3.47).
+// The queue costs where most units draw, with a state and an age store and an
+// atomic for each that fires (regular d = 10, N = 1e6, drawn chunk by chunk /
+// queued / in place: 0.5% of the units in E and as many in I 12.3 / 10.8 / 11.7 us,
+// 4% 12.4 / 11.5 / 11.7, 16% 12.4 / 13.0 / 11.8).  Over an epidemic it gains more than
+// it costs.  Choosing by the last step's share of drawing units, with both loops
+// in a kernel, kept neither's time (11.0, 12.1, 12.3 us): longer code, and in
+// mixed layouts spilled registers.
 // Pooling what a workgroup's wavefronts have left costs a barrier and a
 // search, more than the rounds it saves (N = 1e6 9.6 / 10.0).
 //  q[i].x: the rate, or the age of a unit whose hazard is yet to be evaluated;
 //  q[i].y: lane | pass << 6 | state << 29 | DRAW_EVAL, the pass's chunk being
 //          that of walk position wave + pass * waves.
-constexpr bool draws_in_place(bool weighted, bool shed) { return weighted || shed; }
+constexpr bool draws_in_place(bool weighted, bool shed, int mode) { return weighted || shed || mode == MODE_STREAM; }
 constexpr uint32_t DRAWQ = 128; // at most 63 left over plus one pass's 64
 constexpr uint32_t DRAW_EVAL = 0x80000000u;
 struct DrawCtx {
@@ -902,6 +914,20 @@ __device__ __forceinline__ bool draw_unit(const StepArgs& a, uint32_t id, uint32
     asm volatile("" : "+s"(k0), "+s"(k1), "+s"(ks));
     const uint32_t w = fsd::philox4x32_10(make_uint4(id, ks, rep, 0u), k0, k1).x >> 8;
     return fsd::bernoulli((float)w * 0x1p-24f, lam * dt);
+}
+
+// Units that fired: those entering or leaving I are queued for their pushes
+// into the next step's deltas of the binned rows that list their node.
+__device__ __forceinline__ void queue_pushes(const StepArgs& a, HubCtx& H, uint32_t lane, bool fire, uint32_t x, uint32_t unit)
+{
+    const bool push = fire && x != (uint32_t)ST_S;
+    const unsigned long long pm = __ballot(push);
+    if (pm == 0ull) return;
+    const uint32_t cnt = (uint32_t)__popcll(pm);
+    if (H.n + cnt > PUSHQ) flush_pushes(a, H, lane);
+    if (push)
+        H.q[H.n + (uint32_t)__popcll(pm & ((1ull << lane) - 1ull))] = unit | (x == (uint32_t)ST_I ? 0x80000000u : 0u);
+    H.n += cnt;
 }
 
 // Draws the last m (<= 64) queued units, one per lane: Bernoulli tau-leap, fire
@@ -950,20 +976,7 @@ __device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32
         if (x != (uint32_t)ST_S)
             __hip_atomic_fetch_xor(&bits_out[unit >> 5], 1u << (unit & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    if (HUBS && H.on) {
-        // a unit entering or leaving I is queued for its pushes into the
-        // next step's deltas of the binned rows that list its node
-        const bool push = fire && x != (uint32_t)ST_S;
-        const unsigned long long pm = __ballot(push);
-        if (pm != 0ull) {
-            const uint32_t cnt = (uint32_t)__popcll(pm);
-            if (H.n + cnt > PUSHQ) flush_pushes(a, H, lane);
-            if (push)
-                H.q[H.n + (uint32_t)__popcll(pm & ((1ull << lane) - 1ull))] =
-                    unit | (x == (uint32_t)ST_I ? 0x80000000u : 0u);
-            H.n += cnt;
-        }
-    }
+    if (HUBS && H.on) queue_pushes(a, H, lane, fire, x, unit);
 }
 
 // Everything of one pass after its loads were issued but the queued draws: rates
@@ -971,12 +984,12 @@ __device__ __forceinline__ void draw_batch(const StepArgs& a, DrawCtx& Q, uint32
 // or their queue, the ages and infectivity words of the units that have not
 // fired, (with SHED) the next s(tau) of the infectious units, and the chunk's live
 // flag for compaction.
-template <int STORAGE, bool WEIGHTED, int MODE, int UD, bool SHED, bool EXTRA, int PB, bool FIRST, class age_t>
+template <int STORAGE, bool WEIGHTED, int MODE, int UD, bool SHED, bool EXTRA, int PB, bool FIRST, bool IN_PLACE, class age_t>
 __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t>& P, uint32_t lane,
                                              const uint32_t* __restrict__ s_bits, rsrc_t gbits, rsrc_t shedr,
                                              void* __restrict__ shed_out, const ShedPre& sv, const ShedDev& sdv,
                                              unsigned long long* __restrict__ bits_out, uint32_t k, uint32_t* s_cnt,
-                                             float dt, float& lmax, const HubCtx& H, DrawCtx& Q)
+                                             float dt, float& lmax, HubCtx& H, DrawCtx& Q)
 {
     constexpr bool UNIFORM = UD != 0;
     using state_t = typename Store<STORAGE>::state_t;
@@ -1021,7 +1034,7 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
 
         // 3.-4. the draws (no draw at lambda = 0): in place, or queued
         bool fire = false;
-        const bool here = draws_in_place(WEIGHTED, SHED) || (UNIFORM && FIRST && Q.single);
+        const bool here = IN_PLACE || (UNIFORM && FIRST && Q.single);
         if (here && __builtin_expect(__ballot(miss) != 0ull, 0)) {
             if (miss) {
                 lam = unit_hazard(a.hz_dev, a.same_kind, age_units(ag), x == ST_I);
@@ -1036,6 +1049,7 @@ __device__ __forceinline__ void process_pass(const StepArgs& a, const Pass<age_t
                 opaque_uniform((state_t*)a.state)[unit] = (state_t)(x + 1);
                 atomicAdd(&s_cnt[(unit & (R - 1)) * 4u + (uint32_t)x], 1u); // LDS
             }
+            if (IN_PLACE && !UNIFORM && !WEIGHTED && !SHED && H.on) queue_pushes(a, H, lane, fire, (uint32_t)x, unit);
         }
         const int xn = x + (fire ? 1 : 0);
         const bool need = !here && (miss || lam > 0.0f);
@@ -1107,7 +1121,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
 {
     constexpr bool UNIFORM = UD != 0;
     constexpr bool USE_LDS = MODE != MODE_STREAM;
-    constexpr bool IN_PLACE = draws_in_place(WEIGHTED, SHED), ORG = IN_PLACE && !UNIFORM;
+    constexpr bool QUEUED = !draws_in_place(WEIGHTED, SHED, MODE);
     using age_t = typename Store<STORAGE>::age_t;
     constexpr int NW = TPB / 64;
     static_assert(PB == 0 || !WEIGHTED, "packed columns: unit weights only");
@@ -1115,7 +1129,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     __shared__ uint32_t s_cnt[4 * 64];
     __shared__ __attribute__((aligned(16))) uint32_t s_bits[USE_LDS ? RESIDENT_BITS / 32 : 4];
     static_assert(SUMMARY_BITS <= RESIDENT_BITS, "the summary shares the LDS bitmap array");
-    __shared__ uint2 s_draw[IN_PLACE ? 1 : NW][IN_PLACE ? 1 : DRAWQ];
+    __shared__ uint2 s_draw[QUEUED ? NW : 1][QUEUED ? DRAWQ : 1];
     // pushed pressure of binned rows: per-wavefront push queue and flush tables
     constexpr bool HUBS = !UNIFORM && !WEIGHTED && !SHED;
     __shared__ uint32_t s_pq[HUBS ? NW : 1][HUBS ? PUSHQ : 1];
@@ -1190,7 +1204,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
             ahead.my[u] = m.y;
         }
     }
-    issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
+    issue_pass<STORAGE, UD, EXTRA, PB, !QUEUED && !UNIFORM>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
     for (uint32_t i = tid; i < 4 * R; i += tpb) s_cnt[i] = 0;
     if (USE_LDS) {
         // 16 bytes per lane straight into LDS: wave w fills the blocks of 64
@@ -1227,14 +1241,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     }
     issue_table<UNIFORM>(a, tv, P, lane);
 
-    DrawCtx Q{s_draw[IN_PLACE ? 0 : wave], 0u, 0u, wave_id, nwaves, walk <= nwaves};
-    // whole wavefronts of draws, and after the wavefront's last pass the rest
-    auto draws = [&](bool last) {
-        if constexpr (!IN_PLACE)
-            while (Q.n >= (last ? 1u : 64u))
-                draw_batch<STORAGE, UNIFORM, EXTRA, HUBS>(a, Q, min(Q.n, 64u), lane, (uint32_t)k, (uint32_t*)bo, s_cnt,
-                                                          dt, lmax, H);
-    };
+    DrawCtx Q{s_draw[QUEUED ? wave : 0], 0u, 0u, wave_id, nwaves, walk <= nwaves};
     static_assert(CU == 1, "walk position of a queued draw: one chunk per pass");
 
     // passes: the loads of the next pass are issued (always: a pass past the
@@ -1245,34 +1252,46 @@ __device__ __forceinline__ void step_body(const StepArgs& a, uint32_t block, uin
     // before the next pass's loads are issued
     constexpr bool SPLIT = SHED && MODE == MODE_RESIDENT;
     ShedPre sv;
-    for (;;) {
-        if (first >= walk) break;
-        if (SPLIT) shed_pre<STORAGE, UD, PB>(a, P, lane, s_bits, shedr, sv);
-        if (PREFETCH)
-            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P1,
-                                                     ahead, H);
-        process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, true>(a, P, lane, s_bits, gbits, shedr, shed_out,
-                                                                          sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax, H,
-                                                                          Q);
-        first += stride;
-        draws(first >= walk);
-        if (first >= walk) break;
-        if (!PREFETCH)
-            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P1, ahead, H);
-        issue_table<UNIFORM>(a, tv, P1, lane);
-        if (SPLIT) shed_pre<STORAGE, UD, PB>(a, P1, lane, s_bits, shedr, sv);
-        if (PREFETCH)
-            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P,
-                                                ahead, H);
-        process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, false>(a, P1, lane, s_bits, gbits, shedr, shed_out,
-                                                                           sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax,
-                                                                           H, Q);
-        first += stride;
-        draws(first >= walk);
-        if (!PREFETCH && first < walk)
-            issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
-        if (first < walk) issue_table<UNIFORM>(a, tv, P, lane);
-    }
+    // (a template, inlined after the parts of a pass: as a plain loop the shedding
+    // kernel of mixed layouts takes 129 registers, one more than four wavefronts
+    // per SIMD allow, instead of 113: Erdos-Renyi 6, N = 8e5, R = 2 45.6 us, not 41.1)
+    auto walk_chunks = [&](auto in_place) {
+        constexpr bool IN_PLACE = decltype(in_place)::value, ORG = IN_PLACE && !UNIFORM;
+        // whole wavefronts of draws, and after the wavefront's last pass the rest
+        auto draws = [&](bool last) {
+            if constexpr (!IN_PLACE)
+                while (Q.n >= (last ? 1u : 64u))
+                    draw_batch<STORAGE, UNIFORM, EXTRA, HUBS>(a, Q, min(Q.n, 64u), lane, (uint32_t)k, (uint32_t*)bo,
+                                                              s_cnt, dt, lmax, H);
+        };
+        for (;;) {
+            if (first >= walk) break;
+            if (SPLIT) shed_pre<STORAGE, UD, PB>(a, P, lane, s_bits, shedr, sv);
+            if (PREFETCH)
+                issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P1,
+                                                        ahead, H);
+            process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, true, IN_PLACE>(
+                a, P, lane, s_bits, gbits, shedr, shed_out, sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax, H, Q);
+            first += stride;
+            draws(first >= walk);
+            if (first >= walk) break;
+            if (!PREFETCH)
+                issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P1, ahead, H);
+            issue_table<UNIFORM>(a, tv, P1, lane);
+            if (SPLIT) shed_pre<STORAGE, UD, PB>(a, P1, lane, s_bits, shedr, sv);
+            if (PREFETCH)
+                issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first + stride, nwaves, stride, nchunks, walk, total, lane, P,
+                                                        ahead, H);
+            process_pass<STORAGE, WEIGHTED, MODE, UD, SHED, EXTRA, PB, false, IN_PLACE>(
+                a, P1, lane, s_bits, gbits, shedr, shed_out, sv, sdv, bo, (uint32_t)k, s_cnt, dt, lmax, H, Q);
+            first += stride;
+            draws(first >= walk);
+            if (!PREFETCH && first < walk)
+                issue_pass<STORAGE, UD, EXTRA, PB, ORG>(a, first, nwaves, stride, nchunks, walk, total, lane, P, ahead, H);
+            if (first < walk) issue_table<UNIFORM>(a, tv, P, lane);
+        }
+    };
+    walk_chunks(std::bool_constant<!QUEUED>{});
 
     // the queued pushes of binned rows, after the walk (no prefetched load is
     // in flight any more)
