@@ -509,26 +509,31 @@ bool layout_cached(fs_graph* g, int32_t R, int32_t heavy_deg, int32_t seg_edges,
 // (counted in bytes).
 //  Below REPS_CHUNKS chunks a launch is one chain of latencies, which the
 //  variants' shorter one serves better (us per step, variant / replica step:
-//  regular d = 10, N = 3e4, R = 4, 1875 chunks 5.3 / 7.2; Erdos-Renyi 10, N =
-//  1e4, R = 16, 2500 chunks 8.5 / 8.9; N = 1e5, R = 8, 12500 chunks 14.7 /
-//  11.8; Barabasi-Albert 8, N = 6e4, R = 16, 15000 chunks 23.2 / 17.4).  With four
-//  replicas of a uniform graph a load brings only four bits and the LDS
-//  summary screens most edges (regular d = 10, N = 1e6: 37 / 55; on a
-//  Barabasi-Albert graph, which streams, 101 / 51).
+//  Erdos-Renyi 8, 5000 chunks of 16 replicas 8.4 / 7.8, Barabasi-Albert 4 of 64
+//  11.5 / 12.5; 8200 chunks of 16 10.2 / 8.2, of 64 9.7 / 8.4, Barabasi-Albert 4 of 16
+//  15.8 / 13.1).
+//  Uniform graphs gather without the mixed layouts' bookkeeping.  As long as the
+//  LDS holds their bitmap the resident variant wins (regular d = 10, 8200 chunks of
+//  8 replicas 6.5 / 8.3, of 16 6.2 / 7.5; 16300 of 64 9.5 / 9.8, with a third of the
+//  nodes exposed 10.7 / 12.4), and with four replicas, whose bits come four to a
+//  load, or eight the other variants do (d = 10, N = 1e6, R = 4 37 / 55; 200 steps of
+//  R = 8, 25000 chunks 3.47 / 3.91 ms, 40000 4.93 / 5.02).  With 16 or more past
+//  that: 16500 chunks of 16 3.83 / 3.02 ms, 40000 5.01 / 4.15, 100000 8.40 / 8.23.
 //  The widest group shares most work, the narrowest gives small sims more
 //  wavefronts: the widest that leaves REPS_GROUPS of them, REPS_GROUPS16 of 16
-//  chunks (us per step: Barabasi-Albert 4, N = 3e5, R = 16: 4688 groups of 16
-//  33.3, 9375 of 8 34.0, 18750 of 4 38; regular d = 10, N = 2e5, R = 16 compact:
-//  3125 of 16 21.4, 6250 of 8 20.9; Erdos-Renyi 10, N = 1e5, R = 16: 3125 of 8
-//  14.1, 6250 of 4 15.6; N = 3e4, R = 64: 1875 of 16 14.0, 3750 of 8 12.5).
+//  chunks, which is twice what runs at once: between one such round and two,
+//  most of the second idles (us per step, groups of 4 / 8 / 16: Barabasi-Albert 4,
+//  R = 16, 16500 chunks 14.5 / 14.7 / 16.8, 25000 15.9 / 16.6 / 18.4, 65600 28.7 / 25.3 /
+//  27.6, 75000 30.7 / 27.1 / 30.7, 131000 47.5 / 41.5 / 40.6; regular d = 12, R = 64,
+//  25000 14.8 / 11.9 / 12.9, 65600 28.3 / 21.1 / 22.1, 131000 49.5 / 34.3 / 31.4).
 int replica_width(const fs_graph* g, const fs_sim_params& p, int lgR, int32_t limit)
 {
     if (lgR < 2 || g->d_weights || p.shedding != FS_SHED_CONSTANT || p.adaptive || p.record_rates || p.compaction)
         return -1;
     if (std::min(limit, g->max_degree) > fsi::REPS_MAX_DEG) return -1;
-    const size_t chunks = (((size_t)g->n << lgR) + 63) / 64;
+    const size_t units = (size_t)g->n << lgR, chunks = (units + 63) / 64;
     const bool uniform = g->min_degree == g->max_degree && g->max_degree <= fsi::UNIFORM_MAX_DEG;
-    if (chunks < fsi::REPS_CHUNKS || (uniform && lgR < 3)) return -1;
+    if (chunks < fsi::REPS_CHUNKS || (uniform && (lgR < 4 || units <= fsi::RESIDENT_BITS))) return -1;
     int w = std::min(lgR, 4);
     while (w > 2 && (chunks >> w) < (w == 4 ? fsi::REPS_GROUPS16 : fsi::REPS_GROUPS)) --w;
     return w;
