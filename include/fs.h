@@ -193,8 +193,9 @@ typedef struct fs_sim_params {
                                 group of units screens the bitmap reads), 0 = automatic:
                                 resident when it fits, else summary for adaptive steps,
                                 bitmaps over 8 MB, uniform-degree graphs with at most
-                                4 replicas, or unit weights with at most 2, else
-                                streaming.  Results are identical. */
+                                4 replicas, or unit weights with at most 2 (with
+                                age-dependent shedding and binned rows, from 5 * 2^19
+                                units on), else streaming.  Results are identical. */
     int32_t heavy_degree;    /* degree bins: rows with more incoming edges than this get
                                 their pressure from the heavy-row kernel (segments of
                                 segment_edges edges, one wavefront each); 0 = 64,

@@ -42,6 +42,9 @@ constexpr int32_t REPS_MAX_DEG = 127;
 constexpr size_t REPS_CHUNKS = 8192;
 constexpr size_t REPS_GROUPS = 3072;
 constexpr size_t REPS_GROUPS16 = 8192; // (groups of 16 chunks)
+// The units past which the automatic variant of a shedding sim with binned rows
+// is the summary.
+constexpr size_t SHED_SUMMARY_UNITS = (size_t)5 << 19;
 // Bitmaps are allocated in whole 512-unit tiles (8 words of 64 bits).
 constexpr uint32_t BITMAP_TILE = 512;
 // Active-chunk compaction: the refresh runs one workgroup of WG_REFRESH

@@ -1477,15 +1477,22 @@ fs_status fs_sim_create(fs_graph* g, const fs_sim_params* p, fs_sim** out)
     //    empty group also where a quarter of the units is infectious (Erdos-Renyi
     //    8, N = 1.2e6 42 / 23 with few infectious units, 42 / 29 with many, N =
     //    3e6 103 / 36 and 101 / 51; Barabasi-Albert 4, N = 3e6 103 / 60 and 95 /
-    //    65; Erdos-Renyi 8, N = 1e6, R = 2 52 / 28 and 52 / 33; with shedding, N =
-    //    1.1e6 44 / 42, with compaction, Barabasi-Albert 4, N = 1.1e6 44 / 43);
+    //    65; Erdos-Renyi 8, N = 1e6, R = 2 52 / 28 and 52 / 33; with compaction,
+    //    Barabasi-Albert 4, N = 1.1e6 44 / 43); with shedding, unless rows are
+    //    binned, whose segments read every source's value whatever the summary
+    //    says, and the sim is small (150 steps: Erdos-Renyi 6, N = 1.1e6 5.65 /
+    //    5.46 ms, 12, N = 1.6e6 12.0 / 10.0; Barabasi-Albert 2, N = 1.1e6 7.6 / 9.0,
+    //    1.6e6 9.4 / 10.4, 2.8e6 13.4 / 12.9; 5, N = 8e5, R = 2 11.5 / 12.5, N =
+    //    1.4e6, R = 2 17.6 / 17.0);
     // else the streaming variant: weighted rows gather binned rows as float
     // partials and read a weight per edge whatever the summary says
     // (Barabasi-Albert 5, N = 1.1e6 55 / 60), and once more replicas share
     // bitmap words few groups are empty and its higher occupancy wins.
     const bool uniform = g->min_degree == g->max_degree && g->max_degree <= fsi::UNIFORM_MAX_DEG;
     const bool summary_large = p->adaptive || bitmap_words(units) * 8 > ((size_t)8 << 20) || (uniform && R <= 4);
-    const bool summary_auto = summary_large || (R <= 2 && !g->d_weights);
+    const bool binned = g->max_degree > light_limit(p->heavy_degree == 0 ? 64 : p->heavy_degree);
+    const bool summary_auto =
+        summary_large || (R <= 2 && !g->d_weights && (!shedding || !binned || units >= fsi::SHED_SUMMARY_UNITS));
     s->stream_too = p->variant == 0 && !fits_lds && !summary_large;
     s->mode = p->variant == 1 ? fsi::MODE_STREAM
             : p->variant == 2 ? fsi::MODE_RESIDENT
