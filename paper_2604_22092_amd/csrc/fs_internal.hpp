@@ -21,7 +21,8 @@ constexpr int RED_TPB = 1024;
 //  MODE_SUMMARY  an LDS summary with one bit per group of units (set when any
 //                unit of the group is infectious; at most SUMMARY_BITS bits)
 //                screens the reads of the bitmap, which stays in global memory.
-// The two LDS variants run one RESIDENT_TPB-thread workgroup per compute unit.
+// The two LDS variants run at most one workgroup per compute unit, of 64 to
+// RESIDENT_TPB threads.
 enum : int32_t { MODE_STREAM = 0, MODE_RESIDENT = 1, MODE_SUMMARY = 2 };
 constexpr int STREAM_TPB = 256;
 constexpr int RESIDENT_TPB = 1024;

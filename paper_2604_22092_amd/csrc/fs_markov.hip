@@ -680,7 +680,7 @@ fs_status fs_markov_create(fs_graph* g, const fs_markov_params* p, fs_markov** o
         (e = dev_alloc((void**)&m->d_pending, padded * 4)) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_wcnt, (size_t)m->G * sizeof(uint4))) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_ev_cnt, (size_t)m->G * 4)) != hipSuccess ||
-        (e = dev_alloc((void**)&m->d_fired, ((size_t)m->G + 1) * 4)) != hipSuccess ||
+        (e = dev_alloc((void**)&m->d_fired, (size_t)m->G * 4)) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_rpart, (size_t)m->G * sizeof(uint4))) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_part, part_words * 4)) != hipSuccess ||
         (e = dev_alloc((void**)&m->d_hist, (size_t)m->H * 16)) != hipSuccess ||
@@ -693,7 +693,7 @@ fs_status fs_markov_create(fs_graph* g, const fs_markov_params* p, fs_markov** o
         (e = hipMemsetAsync(m->d_infl, 0, padded * 4, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_pending, 0, padded * 4, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_ev_cnt, 0, (size_t)m->G * 4, m->stream)) != hipSuccess ||
-        (e = hipMemsetAsync(m->d_fired, 0, ((size_t)m->G + 1) * 4, m->stream)) != hipSuccess ||
+        (e = hipMemsetAsync(m->d_fired, 0, (size_t)m->G * 4, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_hist, 0, (size_t)m->H * 16, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_tau, 0, (size_t)m->H * 4, m->stream)) != hipSuccess ||
         (e = hipMemsetAsync(m->d_evh, 0, (size_t)m->H * 4, m->stream)) != hipSuccess ||
