@@ -33,7 +33,7 @@
 // state -> atomic.  Draws, pushes and rates as three launches with one lane per
 // node and one per event took 8.1 + 9.7 + 4.8 us (Erdos-Renyi d = 8, SIR, 600
 // steps); four nodes per lane loaded at once, draws packed and eight lanes per
-// event take 7.8 + 4.2 us (the whole run 14.3 -> 7.7 ms).
+// event take 7.9 + 4.5 us (loaded, stepped and read 15.3 -> 7.9 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -18,13 +18,15 @@
 //          every 64 of them get one wavefront of Philox and the comparison.
 // A wavefront owns a group of W chunks (64 W consecutive units).
 //
-// Measured (traced step launches, one MI355X): Barabasi-Albert m = 4, N = 3e5,
-// 16 replicas, FP32 56.0 -> 33.3 us (89 vector instructions per chunk); m = 5,
-// N = 1e6, 16 replicas 172 -> 88 us; Erdos-Renyi mean degree 10, N = 3e4, 64
-// replicas 25.8 -> 12.5 us.  What is left there is the latency of the chain
-// columns -> bits -> bytes -> units (5 of 14 us of a wavefront's life in the
-// gather, one L1 lookup per edge and compute unit and cycle) and, at N = 1e6,
-// the state and age traffic.
+// Measured (traced step launches, one MI355X, general step / replica step):
+// Barabasi-Albert m = 4, N = 3e5, 16 replicas, FP32 56.0 / 29.5 us over 300 steps
+// of an epidemic and 52 / 27 with few infectious units (111 vector instructions
+// per chunk); m = 5, N = 1e6, 16 replicas 155 / 74 us; Erdos-Renyi mean degree 10,
+// N = 3e4, 64 replicas 23.4 / 11.4 us.  At m = 4 wavefronts wait for memory 42% of
+// their cycles and to issue 32%, and move 2.6 TB/s: what is left there is the
+// latency of the chain columns -> bits -> bytes -> units (5 of 14 us of a
+// wavefront's life in the gather, one L1 lookup per edge and compute unit and
+// cycle) and the issue of the draws; at N = 1e6, the state and age traffic.
 #pragma once
 
 #include "fs_step.hpp"
@@ -39,7 +41,7 @@ constexpr uint32_t REPS_TPB = STREAM_TPB;
 // none, so five wavefronts share a SIMD: the 5000 groups of regular d = 6, N =
 // 2e4, R = 64 run at once (compact, 11.3 us per step with four, 9.3 with five).
 // Groups of 16 need the four chunks' loads in flight more (Barabasi-Albert 4, N =
-// 3e5, R = 16: 33.7 us, two chunks and five wavefronts 35.2).  Draws queued: at
+// 3e5, R = 16 in groups of 16: 33.7 us, two chunks and five wavefronts 35.2).  Draws queued: at
 // most 63 left over plus every unit of those chunks.
 constexpr int reps_ns(int lgw) { return lgw == 3 ? 2 : 4; }
 constexpr int reps_waves(int lgw) { return lgw == 4 ? 4 : 5; }

@@ -874,11 +874,12 @@ __device__ __forceinline__ float pressure_heavy(const StepArgs& a, uint32_t node
 // Weighted kernels and shedding ones, which spend the pass on the gather's loads,
 // draw in place always (queued / in place: weighted Erdos-Renyi 10, N = 1.5e6 65.0 /
 // 63.6 us, N = 1e5 7.1 / 6.9; weighted Barabasi-Albert 4, N = 1.5e6 66.7 / 64.5;
-// shedding, regular d = 13, N = 1.5e6 77.8 / 74.6, N = 3e5 14.0 / 13.7; weighted
-// Erdos-Renyi 10, N = 2e5, R = 4, an exception, 18.2 / 18.5), and so do streaming
-// ones, whose sims with several replicas have one or two chunks per wavefront and
-// those with many waited for the gather (200 steps of regular d = 10, R = 8, 16500
-// chunks 3.36 / 2.95 ms, 25000 3.87 / 3.47).
+// shedding, regular d = 13, N = 1.5e6 77.8 / 74.6, N = 3e5 14.0 / 13.7; two
+// exceptions, weighted Erdos-Renyi 10, N = 2e5, R = 4 18.2 / 18.5 and shedding,
+// regular d = 10, N = 1e6 12.3 / 12.5), and so do streaming ones, whose sims with
+// several replicas have one or two chunks per wavefront and those with many waited
+// for the gather (200 steps of regular d = 10, R = 8, 16500 chunks 3.36 / 2.95 ms,
+// 25000 3.87 / 3.47).
 // The queue costs where most units draw, with a state and an age store and an
 // atomic for each that fires (regular d = 10, N = 1e6, drawn chunk by chunk /
 // queued / in place: 0.5% of the units in E and as many in I 12.3 / 10.8 / 11.7 us,
